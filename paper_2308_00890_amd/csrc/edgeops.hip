@@ -193,10 +193,7 @@ __global__ __launch_bounds__(256) void k_edge_softmax(int n, const int32_t *ptr,
 {
     op.amax = 0.0f;
     walk_rows<GROUP>(ptr, n, op);
-    if (absmax) {
-        const float m = tango_wave_max(op.amax);
-        if (threadIdx.x % TANGO_WAVE == 0 && m > 0.0f) tango_atomic_max_nonneg(absmax, m);
-    }
+    if (absmax) tango_block_max_update(op.amax, absmax);
 }
 
 template <int H>

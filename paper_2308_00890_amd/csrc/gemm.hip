@@ -229,8 +229,7 @@ __global__ __launch_bounds__(256) void k_qgemm_fused(fused_args a)
     }
     if (a.absmax_C) {
         float m = static_cast<float>(maxabs) * sc;  // conversion and product are monotone
-        m = tango_wave_max(m);
-        if (lane == 0 && m > 0.0f) tango_atomic_max_nonneg(a.absmax_C, m);
+        tango_block_max_update(m, a.absmax_C);
     }
 }
 

@@ -6,6 +6,8 @@
 
 namespace {
 
+constexpr int ABSMAX_THREADS = 1024, ABSMAX_BLOCKS = 256;  // see k_absmax
+
 __global__ void k_fill_u32(uint32_t *p, uint32_t v, int64_t n)
 {
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
@@ -28,8 +30,11 @@ __device__ inline float4 tango_mask4b(const float4 a, const uint32_t bits)
 // VEC = 4: x is 16-byte aligned and float4 loads are used for the body.
 // MASKED = 1: element i counts as 0 where mask[i] <= 0 (the gradient behind a ReLU whose output is `mask`).
 // MASKED = 2: the same with mask_bits, bit i set where the ReLU's output is positive (n a multiple of 8).
+// Bound by HBM.  Few, large workgroups (one of 1,024 threads per CU) because every workgroup ends with an update of the
+// one result word and those queue up; four loads per thread in flight are enough with all 16 waves of a workgroup resident
+// (87 MB: 53 us with 4,096 workgroups of 256 threads, 34 us with 256 of 1,024).
 template <int VEC, int MASKED = 0>
-__global__ __launch_bounds__(256) void k_absmax(const float *__restrict__ x, size_t n, float *out,
+__global__ __launch_bounds__(ABSMAX_THREADS) void k_absmax(const float *__restrict__ x, size_t n, float *out,
                                                 const float *__restrict__ mask = nullptr,
                                                 const uint8_t *__restrict__ mask_bits = nullptr)
 {
@@ -40,9 +45,8 @@ __global__ __launch_bounds__(256) void k_absmax(const float *__restrict__ x, siz
         const size_t n4 = n / 4;
         const float4 *x4 = reinterpret_cast<const float4 *>(x);
         size_t i = tid;
-        // eight independent loads per iteration keep enough bytes in flight to cover the memory latency
         const float4 *k4 = reinterpret_cast<const float4 *>(mask);
-        constexpr int UA = MASKED ? 4 : 8;
+        constexpr int UA = 4;
         for (; i + (UA - 1) * nthr < n4; i += UA * nthr) {
             float4 a[UA], k[UA];
 #pragma unroll
@@ -68,15 +72,7 @@ __global__ __launch_bounds__(256) void k_absmax(const float *__restrict__ x, siz
     } else {
         for (size_t j = tid; j < n; j += nthr) m = fmaxf(m, (MASKED != 1 || mask[j] > 0.0f) ? fabsf(x[j]) : 0.0f);
     }
-    m = tango_wave_max(m);
-    __shared__ float part[4];
-    const int wave = threadIdx.x / TANGO_WAVE, lane = threadIdx.x % TANGO_WAVE;
-    if (lane == 0) part[wave] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        m = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
-        if (m > 0.0f) tango_atomic_max_nonneg(out, m);
-    }
+    tango_block_max_update(m, out);
 }
 
 // Vector path: x 16-byte aligned, q 8-byte aligned.  One thread-iteration = 8 elements.
@@ -237,8 +233,7 @@ __global__ __launch_bounds__(256) void k_relu(const float *__restrict__ x, size_
         m = fmaxf(m, v);
     }
     if (absmax) {
-        m = tango_wave_max(m);
-        if (threadIdx.x % TANGO_WAVE == 0 && m > 0.0f) tango_atomic_max_nonneg(absmax, m);
+        tango_block_max_update(m, absmax);
     }
 }
 
@@ -381,9 +376,9 @@ int tango_absmax_accumulate_async(const float *x, size_t n, float *out, hipStrea
 {
     if (n == 0) return TANGO_OK;
     if (tango_aligned(x, 16))
-        k_absmax<4><<<tango_grid_for(n / 4 + 1, 256 * 2), 256, 0, st>>>(x, n, out);
+        k_absmax<4><<<tango_grid_for(n / 4 + 1, ABSMAX_THREADS, ABSMAX_BLOCKS), ABSMAX_THREADS, 0, st>>>(x, n, out);
     else
-        k_absmax<1><<<tango_grid_for(n, 256 * 4), 256, 0, st>>>(x, n, out);
+        k_absmax<1><<<tango_grid_for(n, ABSMAX_THREADS, ABSMAX_BLOCKS), ABSMAX_THREADS, 0, st>>>(x, n, out);
     TANGO_LAUNCH_CHECK();
     return TANGO_OK;
 }
@@ -453,7 +448,7 @@ int tango_quantize_masked_async(const float *x, const float *mask, size_t n, int
     int rc = tango_fill_u32_async(reinterpret_cast<uint32_t *>(absmax_ws), 0u, 1, st);
     if (rc != TANGO_OK) return rc;
     if (n == 0) return tango_quantize_with_absmax_async(x, n, rounding, seed, stream_id, absmax_ws, q, scale_out, st);
-    k_absmax<4, 1><<<tango_grid_for(n / 4 + 1, 256 * 2), 256, 0, st>>>(x, n, absmax_ws, mask);
+    k_absmax<4, 1><<<tango_grid_for(n / 4 + 1, ABSMAX_THREADS, ABSMAX_BLOCKS), ABSMAX_THREADS, 0, st>>>(x, n, absmax_ws, mask);
     TANGO_LAUNCH_CHECK();
     const tango_rng rng = tango_rng_make(seed, stream_id);
     const unsigned grid = tango_grid_for(n / 8 + 1, 256 * 2);
@@ -473,7 +468,7 @@ int tango_quantize_bitmasked_async(const float *x, const uint8_t *mask_bits, siz
     int rc = tango_fill_u32_async(reinterpret_cast<uint32_t *>(absmax_ws), 0u, 1, st);
     if (rc != TANGO_OK) return rc;
     if (n == 0) return tango_quantize_with_absmax_async(x, n, rounding, seed, stream_id, absmax_ws, q, scale_out, st);
-    k_absmax<4, 2><<<tango_grid_for(n / 4 + 1, 256 * 2), 256, 0, st>>>(x, n, absmax_ws, nullptr, mask_bits);
+    k_absmax<4, 2><<<tango_grid_for(n / 4 + 1, ABSMAX_THREADS, ABSMAX_BLOCKS), ABSMAX_THREADS, 0, st>>>(x, n, absmax_ws, nullptr, mask_bits);
     TANGO_LAUNCH_CHECK();
     const tango_rng rng = tango_rng_make(seed, stream_id);
     const unsigned grid = tango_grid_for(n / 8 + 1, 256 * 2);
