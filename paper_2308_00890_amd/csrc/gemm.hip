@@ -327,22 +327,16 @@ __global__ __launch_bounds__(256) void k_quantize_b_small(int K, int N, int Kp, 
 }
 
 // src (R x C int8) -> dst (Rp x Cp bytes, Cp a multiple of 4), every byte of dst written (zero in the padding); the same
-// launch clears n_zero 32-bit words at zero_words (the weight-gradient accumulator) and one more at zero_one (an abs-max),
-// either of which may be NULL.
+// launch clears one word at zero_one (an abs-max; may be NULL).
 __global__ __launch_bounds__(256) void k_pad_copy_i8(int R, int C, int Rp, int Cp, const int8_t *__restrict__ src,
-                                                     int8_t *__restrict__ dst, uint32_t *zero_words, int64_t n_zero,
-                                                     uint32_t *zero_one, tango_colsum_job tail)
+                                                     int8_t *__restrict__ dst, uint32_t *zero_one, tango_colsum_job tail)
 {
     if (blockIdx.x == gridDim.x - 1) tango_colsum_apply(tail);  // (a job left over from the previous step of the chain)
     const int wpr = Cp / 4;
     const int64_t words = static_cast<int64_t>(Rp) * wpr;
     if (blockIdx.x == 0 && threadIdx.x == 0 && zero_one) *zero_one = 0u;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < words + n_zero;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < words;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        if (i >= words) {
-            zero_words[i - words] = 0u;
-            continue;
-        }
         const int r = static_cast<int>(i / wpr), c0 = static_cast<int>(i - static_cast<int64_t>(r) * wpr) * 4;
         uint32_t word = 0;
         if (r < R) {
@@ -354,12 +348,18 @@ __global__ __launch_bounds__(256) void k_pad_copy_i8(int R, int C, int Rp, int C
 }
 
 // ---------------------------------------------------------------------------
-// acc[k][n] += sum_{m in slab} P[m][k] * Q[m][n]  (P: M x K, Q: M x N, both int8 row-major):
+// part[slab][k][n] = sum_{m in slab} P[m][k] * Q[m][n]  (P: M x K, Q: M x N, both int8 row-major):
 // the weight-gradient product, whose reduction runs over the nodes.  Both
 // operands are read with the reduction index as the slow one, so 4x4 byte
 // blocks are transposed in registers (v_perm_b32) on their way into LDS.
-// Workgroup = 128 x 128 output tile x one slab of rows; partial tiles are added
-// with int32 atomics (exact, order-free).
+// Workgroup = 128 x 128 output tile x one slab of rows; the slabs' int32 tiles are stored side by side and summed in
+// 64 bits by k_sum_slabs.
+//
+// What bounds it: the int8 operands are 5-10 us of HBM time at the sizes of a layer and the matrix work is less, so what
+// counts is the latency of a step and what happens to the partial tiles.  The rows of the next two steps are therefore on
+// their way while a step is multiplied (two LDS buffers, one barrier a step), and the partial tiles are plain stores.
+// Measured with the sum of the slabs, against 64-bit atomics and no step ahead: 169,343 x 128 x 256 75 -> 28 us,
+// 232,965 x 602 x 256 313 -> 116 us, 2,449,029 x 384 x 384 825 -> 575 us (3.3 TB/s of operand bytes, each read once).
 // ---------------------------------------------------------------------------
 constexpr int TT = 128;          // output tile edge
 constexpr int MS = 64;           // reduction rows per step
@@ -393,11 +393,11 @@ __device__ inline void transpose4x4(uint32_t r0, uint32_t r1, uint32_t r2, uint3
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_gemm_tn(int64_t M, int K, int N, const int8_t *__restrict__ P,
-                                                 const int8_t *__restrict__ Q, long long *acc_out, int64_t slab_rows,
+                                                 const int8_t *__restrict__ Q, int32_t *__restrict__ part, int64_t slab_rows,
                                                  int tiles_k, int tiles_n)
 {
-    __shared__ __align__(16) int8_t Pt[TT * LDM];
-    __shared__ __align__(16) int8_t Qt[TT * LDM];
+    __shared__ __align__(16) int8_t Pt[2][TT * LDM];
+    __shared__ __align__(16) int8_t Qt[2][TT * LDM];
     const int tid = threadIdx.x, lane = tid % TANGO_WAVE, wave = tid / TANGO_WAVE;
     // Workgroups go to the 8 XCDs in turn, each with an L2 of its own: the output tiles of one slab of rows read the same
     // rows of P and Q, so they are given to workgroups 8 apart (same XCD, consecutive there) and share those rows in
@@ -413,57 +413,102 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int rbase = (wave / 2) * 64, cbase = (wave % 2) * 64;
     v16i acc00 = {0}, acc01 = {0}, acc10 = {0}, acc11 = {0};
 
-    for (int64_t m0 = m_begin; m0 < m_end; m0 += MS) {
-        // stage: waves 0-1 transpose the P slab, waves 2-3 the Q slab.  A thread takes one quad of columns (32 per tile,
-        // consecutive lanes = 128 contiguous bytes of a row) and 16 consecutive rows: four 4x4 byte transposes give, for
-        // each of its 4 columns, the 16 row bytes that one MFMA operand read wants - one 16-byte LDS store each.  The
-        // 16-byte chunk index is XORed with (row / 16) % 4 so that neither these stores (lanes 4 rows apart) nor the
-        // operand reads (lanes 1 row apart) collide in the LDS banks (64 banks of 4 bytes; a 16-byte access is served
-        // sixteen lanes per cycle, and with the 80-byte row stride sixteen consecutive rows - or sixteen rows 4 apart -
-        // then cover all 64 banks exactly once).
-        {
-            const int half = tid / 128, t128 = tid % 128;
-            const int qb = t128 % 32, qa = t128 / 32;
-            const int8_t *src = half ? Q : P;
-            const int ld = half ? N : K;
-            const int c0 = (half ? n0 : k0) + 4 * qb;
-            int8_t *dstT = half ? Qt : Pt;
-            uint32_t w[16];
-            if (m0 + MS <= m_end && c0 + 3 < ld) {
-                // interior: sixteen independent loads, no per-load bounds check between them
-                const int8_t *p0 = src + (m0 + 16 * qa) * ld + c0;
+    // stage: waves 0-1 transpose the P slab, waves 2-3 the Q slab.  A thread takes one quad of columns (32 per tile,
+    // consecutive lanes = 128 contiguous bytes of a row) and 16 consecutive rows: four 4x4 byte transposes give, for
+    // each of its 4 columns, the 16 row bytes that one MFMA operand read wants - one 16-byte LDS store each.  The
+    // 16-byte chunk index is XORed with (row / 16) % 4 so that neither these stores (lanes 4 rows apart) nor the
+    // operand reads (lanes 1 row apart) collide in the LDS banks (64 banks of 4 bytes; a 16-byte access is served
+    // sixteen lanes per cycle, and with the 80-byte row stride sixteen consecutive rows - or sixteen rows 4 apart -
+    // then cover all 64 banks exactly once).
+    const int half = tid / 128, t128 = tid % 128;
+    const int qb = t128 % 32, qa = t128 / 32;
+    const int8_t *src = half ? Q : P;
+    const int ld = half ? N : K;
+    const int c0 = (half ? n0 : k0) + 4 * qb;
+    // a quad that reaches over the last column is read from the row's last four bytes and shifted, one beyond it reads them
+    // too and counts as zero (if either operand has rows of fewer than four bytes, all waves take the byte-wise path)
+    const int c_at = min(c0, ld - 4);
+    const int over = 8 * (c0 - c_at);  // bits to shift out
+    const bool ragged = k0 + TT > K || n0 + TT > N;
+    auto request = [&](int64_t m0, uint32_t (&w)[16]) {
+        const int8_t *p0 = src + (m0 + 16 * qa) * ld + c_at;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) w[i] = reinterpret_cast<const unaligned_u32 *>(p0 + static_cast<int64_t>(i) * ld)->v;
-            } else {
+        for (int i = 0; i < 16; ++i) w[i] = reinterpret_cast<const unaligned_u32 *>(p0 + static_cast<int64_t>(i) * ld)->v;
+    };
+    auto to_lds = [&](int buf, const uint32_t (&w)[16]) {
+        int8_t *dstT = half ? Qt[buf] : Pt[buf];
+        uint32_t t[4][4];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) w[i] = load_quad(src, m0 + 16 * qa + i, m_end, ld, c0, ld);
-            }
-            uint32_t t[4][4];
+        for (int b = 0; b < 4; ++b) transpose4x4(w[4 * b], w[4 * b + 1], w[4 * b + 2], w[4 * b + 3], t[b]);
 #pragma unroll
-            for (int b = 0; b < 4; ++b) transpose4x4(w[4 * b], w[4 * b + 1], w[4 * b + 2], w[4 * b + 3], t[b]);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int row = 4 * qb + c;
-                *reinterpret_cast<uint4 *>(dstT + row * LDM + 16 * (qa ^ ((row / 16) % 4))) =
-                    make_uint4(t[0][c], t[1][c], t[2][c], t[3][c]);
-            }
+        for (int c = 0; c < 4; ++c) {
+            const int row = 4 * qb + c;
+            *reinterpret_cast<uint4 *>(dstT + row * LDM + 16 * (qa ^ ((row / 16) % 4))) =
+                make_uint4(t[0][c], t[1][c], t[2][c], t[3][c]);
         }
-        __syncthreads();
+    };
+    auto stage = [&](int buf, uint32_t (&w)[16]) {
+        if (ragged) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) w[i] = over < 32 ? w[i] >> over : 0u;
+        }
+        to_lds(buf, w);
+    };
+    auto multiply = [&](int buf) {
+        const int8_t *Pb = Pt[buf], *Qb = Qt[buf];
 #pragma unroll
         for (int ks = 0; ks < MS; ks += 32) {
             const int mc = ks / 16 + lane / 32;  // 16-byte chunk of the reduction rows
             const int ra = rbase + lane % 32, rb = cbase + lane % 32;
-            const v4i a0 = *reinterpret_cast<const v4i *>(Pt + ra * LDM + 16 * (mc ^ ((ra / 16) % 4)));
-            const v4i a1 = *reinterpret_cast<const v4i *>(Pt + (ra + 32) * LDM + 16 * (mc ^ (((ra + 32) / 16) % 4)));
-            const v4i b0 = *reinterpret_cast<const v4i *>(Qt + rb * LDM + 16 * (mc ^ ((rb / 16) % 4)));
-            const v4i b1 = *reinterpret_cast<const v4i *>(Qt + (rb + 32) * LDM + 16 * (mc ^ (((rb + 32) / 16) % 4)));
+            const v4i a0 = *reinterpret_cast<const v4i *>(Pb + ra * LDM + 16 * (mc ^ ((ra / 16) % 4)));
+            const v4i a1 = *reinterpret_cast<const v4i *>(Pb + (ra + 32) * LDM + 16 * (mc ^ (((ra + 32) / 16) % 4)));
+            const v4i b0 = *reinterpret_cast<const v4i *>(Qb + rb * LDM + 16 * (mc ^ ((rb / 16) % 4)));
+            const v4i b1 = *reinterpret_cast<const v4i *>(Qb + (rb + 32) * LDM + 16 * (mc ^ (((rb + 32) / 16) % 4)));
             acc00 = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc00, 0, 0, 0);
             acc01 = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b1, acc01, 0, 0, 0);
             acc10 = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b0, acc10, 0, 0, 0);
             acc11 = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc11, 0, 0, 0);
         }
+    };
+    // Whole steps, in pairs: while one step is multiplied, the rows of the next two are on their way (a step of a workgroup is
+    // bound by the latency of its loads: 1.4 us with one step of slack).  Requests beyond the last whole step repeat it.
+    const int steps = static_cast<int>((m_end - m_begin + MS - 1) / MS);
+    const int whole = min(K, N) >= 4 ? static_cast<int>((m_end - m_begin) / MS) : 0;
+    if (whole > 0) {
+        uint32_t wa[16], wb[16];
+        const auto row_of = [&](int s) { return m_begin + static_cast<int64_t>(min(s, whole - 1)) * MS; };
+        request(row_of(0), wa);
+        request(row_of(1), wb);
+        stage(0, wa);
+        __syncthreads();
+#pragma unroll 1
+        for (int s = 0; s + 1 < whole; s += 2) {
+            request(row_of(s + 2), wa);
+            multiply(0);
+            stage(1, wb);
+            __syncthreads();
+            request(row_of(s + 3), wb);
+            multiply(1);
+            stage(0, wa);
+            __syncthreads();
+        }
+        if (whole & 1) {
+            multiply(0);
+            __syncthreads();
+        }
+    }
+#pragma unroll 1
+    for (int s = whole; s < steps; ++s) {  // the slab's last rows, fewer than a step (with rows of under four bytes: all of them)
+        const int64_t m0 = m_begin + static_cast<int64_t>(s) * MS;
+        uint32_t w[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) w[i] = load_quad(src, m0 + 16 * qa + i, m_end, ld, c0, ld);
+        to_lds(0, w);
+        __syncthreads();
+        multiply(0);
         __syncthreads();
     }
+    int32_t *mine = part + slab * K * N;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const v16i &acc = t == 0 ? acc00 : (t == 1 ? acc01 : (t == 2 ? acc10 : acc11));
@@ -472,20 +517,66 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int row = k0 + rbase + rb * 32 + (i / 4) * 8 + (lane / 32) * 4 + (i % 4);
-            if (row < K && col < N && acc[i] != 0)
-                atomicAdd(reinterpret_cast<unsigned long long *>(acc_out + static_cast<int64_t>(row) * N + col),
-                          static_cast<unsigned long long>(static_cast<long long>(acc[i])));
+            if (row < K && col < N) mine[static_cast<int64_t>(row) * N + col] = acc[i];
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_dequant_i64(const long long *__restrict__ acc, int64_t n, const float *sa,
-                                                     const float *sb, float *__restrict__ out)
+// out[i] = float(sum over the slabs of part[s][i], in 64 bits) * (sa*sb).  A workgroup takes 32 consecutive outputs, 8
+// lanes of 4 outputs side by side and 32 slabs deep (a thread per output would walk the slabs as one long chain of loads).
+__global__ __launch_bounds__(256) void k_sum_slabs(const int32_t *__restrict__ part, int slabs, int64_t n, const float *sa, const float *sb,
+                                                   float *__restrict__ out)
 {
+    __shared__ long long red[32][33];
     const float sc = (*sa) * (*sb);
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-        out[i] = static_cast<float>(acc[i]) * sc;
+    const int q = threadIdx.x % 8, d = threadIdx.x / 8;
+    for (int64_t base = static_cast<int64_t>(blockIdx.x) * 32; base < n; base += static_cast<int64_t>(gridDim.x) * 32) {
+        const int64_t i = base + 4 * q;
+        long long t[4] = {0, 0, 0, 0};
+        if (n % 4 == 0 && i < n) {
+#pragma unroll 4
+            for (int s = d; s < slabs; s += 32) {
+                const int4 v = *reinterpret_cast<const int4 *>(part + static_cast<int64_t>(s) * n + i);
+                t[0] += v.x; t[1] += v.y; t[2] += v.z; t[3] += v.w;
+            }
+        } else {
+            for (int s = d; s < slabs; s += 32)
+                for (int k = 0; k < 4; ++k)
+                    if (i + k < n) t[k] += part[static_cast<int64_t>(s) * n + i + k];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) red[d][4 * q + k] = t[k];
+        __syncthreads();
+        if (threadIdx.x < 32 && base + threadIdx.x < n) {
+            long long v = 0;
+#pragma unroll 8
+            for (int k = 0; k < 32; ++k) v += red[k][threadIdx.x];
+            out[base + threadIdx.x] = static_cast<float>(v) * sc;
+        }
+        __syncthreads();
+    }
+}
+
+// The slabs of the weight-gradient product.  Each costs a store and a read of a K x N tile of 32-bit sums, so their bytes
+// stay below half of the operands' - but the slabs are enough for one workgroup per CU, and never more than three (what a CU
+// holds), counted per XCD since a slab's tiles go to one XCD.  A slab has at least two steps of rows, and at most 2^17 so that
+// the 32-bit sums stay exact (2^17 * 127^2 < 2^31).
+struct tn_split {
+    int tiles_k, tiles_n;
+    int64_t slab_rows, slabs;
+};
+tn_split split_tn(int64_t M, int64_t N, int64_t K)
+{
+    tn_split t;
+    t.tiles_k = static_cast<int>((K + TT - 1) / TT);
+    t.tiles_n = static_cast<int>((N + TT - 1) / TT);
+    const int64_t tiles = static_cast<int64_t>(t.tiles_k) * t.tiles_n;
+    const int64_t most = 8 * std::max<int64_t>(1, 32 * 3 / tiles), least = 8 * std::max<int64_t>(1, 32 / tiles);
+    int64_t slabs = std::min(most, std::max(least, M * (K + N) / (2 * 4 * K * N) / 8 * 8));
+    slabs = std::max<int64_t>(1, std::min<int64_t>(slabs, M / (2 * MS)));
+    t.slab_rows = std::min<int64_t>(tango_round_up(static_cast<size_t>((M + slabs - 1) / slabs), MS), int64_t(1) << 17);
+    t.slabs = (M + t.slab_rows - 1) / t.slab_rows;
+    return t;
 }
 
 int launch_fused(const fused_args &a_in, int rounding, hipStream_t st)
@@ -633,7 +724,8 @@ extern "C" {
 size_t tango_qgemm_bwd_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
     if (validate_mnk(M, N, K) != TANGO_OK) return 0;
-    return 256 + bt_bytes(K, N) + tango_round_up(static_cast<size_t>(K) * N * sizeof(long long), 256);
+    const size_t part = static_cast<size_t>(split_tn(M, N, K).slabs) * static_cast<size_t>(K) * N * sizeof(int32_t);
+    return 256 + bt_bytes(K, N) + tango_round_up(part, 256);
 }
 
 int tango_qgemm_bwd(int64_t M, int64_t N, int64_t K, const int8_t *A_q, const float *s_A, const int8_t *B_q,
@@ -671,8 +763,7 @@ int tango_qgemm_bwd_masked(int64_t M, int64_t N, int64_t K, const int8_t *A_q, c
     hipStream_t st = tango_stream(stream);
     float *am = static_cast<float *>(ws);
     int8_t *BT = static_cast<int8_t *>(ws) + 256;           // B_q padded: Kp64 rows x Np32 bytes
-    long long *acc = reinterpret_cast<long long *>(BT + bt_bytes(K, N));  // 64-bit sums of the weight gradient
-    bool acc_zeroed = false;
+    int32_t *part = reinterpret_cast<int32_t *>(BT + bt_bytes(K, N));  // the weight gradient's sums, slab by slab
     const float *amp = absmax_dC_in;
     if (!amp) {
         if ((rc = tango_fill_u32_async(reinterpret_cast<uint32_t *>(am), 0u, 1, st)) != TANGO_OK) return rc;
@@ -690,13 +781,11 @@ int tango_qgemm_bwd_masked(int64_t M, int64_t N, int64_t K, const int8_t *A_q, c
         // dA = dC_q . B_q^T: the forward kernel with dC in the role of A and B_q (K x N, rows contiguous along
         // the reduction index n) in the role of the transposed operand.
         const int Rp = static_cast<int>(tango_round_up(N, 32)), Cp = static_cast<int>(tango_round_up(K, 64));
-        // (the padded copy of B_q, the clearing of max|dA| and, if the weight gradient follows, of its accumulator: one launch)
-        const int64_t n_zero = dB ? 2 * K * N : 0;
-        k_pad_copy_i8<<<tango_grid_for(static_cast<size_t>(Cp) * Rp / 4 + n_zero, 256), 256, 0, st>>>(
-            static_cast<int>(K), static_cast<int>(N), Cp, Rp, B_q, BT, reinterpret_cast<uint32_t *>(acc), n_zero,
-            reinterpret_cast<uint32_t *>(absmax_dA), tail ? *tail : tango_colsum_job{nullptr, 0, 0, nullptr, nullptr});
+        // (the padded copy of B_q and the clearing of max|dA|: one launch)
+        k_pad_copy_i8<<<tango_grid_for(static_cast<size_t>(Cp) * Rp / 4, 256), 256, 0, st>>>(
+            static_cast<int>(K), static_cast<int>(N), Cp, Rp, B_q, BT, reinterpret_cast<uint32_t *>(absmax_dA),
+            tail ? *tail : tango_colsum_job{nullptr, 0, 0, nullptr, nullptr});
         TANGO_LAUNCH_CHECK();
-        acc_zeroed = true;
         fused_args a;
         a.M = M; a.N = static_cast<int>(K); a.K = static_cast<int>(N); a.Kp = Rp; a.Np = Cp;
         a.A = dC; a.absmax_A = amp; a.absmax_A_count = 1; a.rng = tango_rng_make(seed, stream_id_dC);
@@ -709,24 +798,11 @@ int tango_qgemm_bwd_masked(int64_t M, int64_t N, int64_t K, const int8_t *A_q, c
     }
     if (dB) {
         // dB = A_q^T . dC_q, reduction over the M rows, split into slabs
-        if (!acc_zeroed && (rc = tango_fill_u32_async(reinterpret_cast<uint32_t *>(acc), 0u, 2 * K * N, st)) != TANGO_OK)
-            return rc;
-        const int tiles_k = static_cast<int>((K + TT - 1) / TT), tiles_n = static_cast<int>((N + TT - 1) / TT);
-        // about 2,048 workgroups in all: enough to fill the chip several times over, and half the 64-bit atomics of 4,096
-        // (measured at 233 k x 602 x 256: 0.38 -> 0.31 ms)
-        int64_t slabs = 2048 / (tiles_k * tiles_n);
-        // at least eight steps per workgroup before its 64 KB of atomics; two where the whole product is a few dozen steps,
-        // which a couple of workgroups would otherwise walk as one long chain of dependent load - transpose - multiply steps
-        slabs = std::min<int64_t>(slabs, M / ((M < 65536 ? 2 : 8) * MS));
-        if (slabs < 1) slabs = 1;
-        // a slab's int32 partial sums stay exact (2^17 rows x 127^2 < 2^31); the slabs are combined in 64 bits
-        int64_t slab_rows = std::min<int64_t>(tango_round_up(static_cast<size_t>((M + slabs - 1) / slabs), MS), int64_t(1) << 17);
-        slabs = (M + slab_rows - 1) / slab_rows;
-        const unsigned grid = static_cast<unsigned>(tiles_k * tiles_n * tango_round_up(static_cast<size_t>(slabs), 8));
-        k_gemm_tn<<<grid, 256, 0, st>>>(M, static_cast<int>(K), static_cast<int>(N), A_q, dC_q, acc, slab_rows, tiles_k,
-                                        tiles_n);
+        const tn_split t = split_tn(M, N, K);
+        const unsigned grid = static_cast<unsigned>(static_cast<int64_t>(t.tiles_k) * t.tiles_n * tango_round_up(static_cast<size_t>(t.slabs), 8));
+        k_gemm_tn<<<grid, 256, 0, st>>>(M, static_cast<int>(K), static_cast<int>(N), A_q, dC_q, part, t.slab_rows, t.tiles_k, t.tiles_n);
         TANGO_LAUNCH_CHECK();
-        k_dequant_i64<<<tango_grid_for(static_cast<size_t>(K) * N, 256), 256, 0, st>>>(acc, K * N, s_A, s_dC, dB);
+        k_sum_slabs<<<tango_grid_for(static_cast<size_t>(K) * N, 32), 256, 0, st>>>(part, static_cast<int>(t.slabs), K * N, s_A, s_dC, dB);
         TANGO_LAUNCH_CHECK();
     }
     return TANGO_OK;

@@ -93,6 +93,31 @@ def test_qgemm_backward(T, M, K, N):
     assert_bit_exact(host(dB2), r["dB"], "dB (alone)")
 
 
+# (M, K, N) for the weight-gradient product: no whole step of 64 rows, one, two and three of them with and without rows left
+# over, rows of fewer than four bytes in either operand, edge tiles whose last quad of columns is cut at each byte, several
+# tiles, and many slabs
+TN_SHAPES = [(63, 3, 130), (64, 5, 1), (65, 130, 3), (127, 4, 127), (128, 129, 47), (129, 47, 4), (191, 501, 2), (192, 128, 128),
+             (193, 7, 255), (256, 130, 6), (1000, 1, 300), (5000, 260, 260), (70001, 12, 9), ((1 << 18) + 70, 4, 5)]
+
+
+@pytest.mark.parametrize("M,K,N", TN_SHAPES)
+def test_weight_gradient_product(T, M, K, N):
+    import torch
+
+    rng = np.random.default_rng(3 * M + 5 * K + N)
+    A_q = rng.integers(-127, 128, size=(M, K), dtype=np.int8)
+    sA, sB = np.float32(0.031), np.float32(1.0)
+    dC = ti.normal((M, N), 41 + N)
+    dC_q, s_dC, dB = empty((M, N), torch.int8), scalar(-1), empty((K, N), torch.float32)
+    ws = workspace(T.tango_qgemm_bwd_workspace_bytes(M, N, K))
+    ws.fill_(0xA5)  # what the workspace holds on entry must not matter
+    B_q = np.zeros((K, N), np.int8)  # not read: the input gradient is not asked for
+    T.tango_qgemm_bwd(dev(A_q), scalar(sA), dev(B_q), scalar(sB), dev(dC), orc.RN, 7, 8, None, dC_q, s_dC, None, dB, ws)
+    torch.cuda.synchronize()
+    r = orc.qgemm_bwd(A_q, sA, B_q, sB, dC, orc.RN, 7, 8)
+    assert_bit_exact(host(dB), r["dB"], "dB")
+
+
 # (M, K, N) for the tiled int8 kernels: one tile, ragged M and N, K not a multiple of 128 (the kernel with register
 # staging), several tiles; K a multiple of 128 (the kernel with direct global -> LDS loads): one, two, three and many
 # K-steps, ragged M and N, eight tile columns (the XCD-aware tile order)
