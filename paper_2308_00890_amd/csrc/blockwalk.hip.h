@@ -1,0 +1,408 @@
+// Aggregation over blocks of 64 edges on the matrix cores (included by sparse.hip after the argument structures).
+//
+// A wavefront walks a chunk of consecutive edges in blocks of 64 and takes one column slice of SW bytes of every gathered
+// row (a slice is one 128-byte line where the row is wide enough).  The 64 row slices of a block go from global memory
+// straight into LDS (global_load_lds_dwordx4), so a whole block is in flight per wave without a register held for it.  The
+// reduction over the edges is a matrix product: v_mfma_i32_16x16x64_i8 with k = the 64 edges, the 16 rows of the left
+// operand = sixteen consecutive graph rows (each holds the weights of its own edges, zero elsewhere), and the columns of the
+// right operand = 16 feature columns, read from LDS with the transposing ds_read_b64_tr_b8.  All row segments of a block
+// are therefore summed at once, whatever their lengths; the sums are exact int32 as before.
+//
+// Measured against the kernels with a lane group per gathered row (main kernels of one aggregation, us): GCN with 169 k nodes and
+// F = 256 153 -> 85; attention forward, the same graph, 4 x 64: 231 -> 93; 256 subgraphs of 1,024 nodes, 2 x 32: 162 -> 92;
+// scale-22 graph, F = 128: 2,066 -> 1,427, F = 32: 1,455 -> 950; 2.4 M nodes, 3 x 128: 4,150 -> 3,780; 115 M edges, 4 x 64:
+// 2,520 -> 2,330 (1,580 of them for the gathers alone).
+//
+// Why: the walk with one lane group per gathered row (k_spmm) spent 10 to 15 vector instructions per edge on byte
+// transposes, dot products and per-row bookkeeping and was bound by their issue and by one load latency per row segment.
+//
+// Why slices: the gathers are bound by what crosses from the L2s to the memory side.  The XCDs' L2s are separate, so when
+// a row has 2, 4 or 8 slices, XCD x works on slice x % slices only and its L2 holds lines of 1/slices of the table: gathers
+// alone (no arithmetic) on the 60 MB table of a graph with 115 M edges took 1.46 instead of 2.04 ms.  Other slice counts
+// are walked one slice after the other over the whole chip.
+#pragma once
+
+typedef int bw_v4i __attribute__((ext_vector_type(4)));
+typedef int bw_v2i __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) bw_v2i bw_lds_v2i;
+
+struct bw_grid {
+    int slices;       // column slices of a row
+    unsigned groups;  // workgroups per slice
+};
+
+// Chunk 16 of row r of a block sits in slot chunk ^ bw_swz(r): the 32 lanes of one LDS cycle of a transposing read (eight rows
+// of two groups of sixteen rows, one 16-byte chunk each) then cover all 64 banks once.
+template <int SW>
+__device__ __forceinline__ int bw_swz(int r)
+{
+    if (SW == 128) return ((r >> 1) & 3) | (((r >> 4) & 1) << 2);
+    if (SW == 64) return ((r >> 2) & 1) | (((r >> 4) & 1) << 1);
+    return (r >> 4) & 1;
+}
+
+// Which slice and which group of chunks this workgroup takes.
+__device__ __forceinline__ void bw_place(const bw_grid &gs, int &slice, unsigned &group)
+{
+    const unsigned b = blockIdx.x;
+    if (gs.slices == 2 || gs.slices == 4 || gs.slices == 8) {
+        const unsigned xcd = b % 8, s = static_cast<unsigned>(gs.slices);
+        slice = static_cast<int>(xcd % s);
+        group = (b / 8) * (8 / s) + xcd / s;
+    } else {
+        slice = static_cast<int>(b / gs.groups);
+        group = b % gs.groups;
+    }
+}
+
+// The 64 row slices of a block into LDS; at: LDS, the table rows of the block's edges (rows of F bytes, X: the slice of row
+// 0), as row numbers or, SMALL (the table is known to end below 4 GB), as byte offsets.
+template <int SW, bool SMALL>
+__device__ __forceinline__ void bw_gather(const int8_t *__restrict__ X, const uint32_t *at, int F, int8_t *tile, int lane)
+{
+    constexpr int CPR = SW / 16, RPI = 64 / CPR;  // chunks of a row slice, rows per load instruction
+    const int rr = lane / CPR, slot = lane % CPR;
+#pragma unroll
+    for (int j = 0; j < CPR; ++j) {
+        const int r = RPI * j + rr;
+        const uint32_t chunk = static_cast<uint32_t>((slot ^ bw_swz<SW>(r)) * 16);
+        const int8_t *from = SMALL ? X + (at[r] + chunk) : X + chunk + static_cast<uint64_t>(at[r]) * static_cast<uint32_t>(F);
+        __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t *>(from), reinterpret_cast<uint32_t *>(tile + 1024 * j), 16, 0, 0);
+    }
+}
+
+// The N (1, 2, 4) consecutive bytes at p as one word; aligned: p is a multiple of N.
+template <int N>
+__device__ __forceinline__ uint32_t bw_load_bytes(const int8_t *p, bool aligned)
+{
+    if (N == 4 && aligned) return *reinterpret_cast<const uint32_t *>(p);
+    if (N == 2 && aligned) return *reinterpret_cast<const uint16_t *>(p);
+    uint32_t w = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) w |= static_cast<uint32_t>(static_cast<uint8_t>(p[j])) << (8 * j);
+    return w;
+}
+
+// Byte masks (0xff / 0) of edges 16*kg .. 16*kg+15 of a block that lie in [lo, hi).
+__device__ __forceinline__ void bw_range_mask(int lo, int hi, int kg, uint32_t (&m)[4])
+{
+    const int l = min(max(lo - 16 * kg, 0), 16), h = min(max(hi - 16 * kg, 0), 16);
+    const uint32_t bits = ((1u << h) - 1u) & ~((1u << l) - 1u);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t ones = __umul24((bits >> (4 * q)) & 15u, 0x204081u) & 0x01010101u;  // bit j of the nibble to byte j
+        m[q] = (ones << 8) - ones;
+    }
+}
+
+// Inclusive running maximum over the lanes.
+__device__ __forceinline__ int bw_scan_max(int v)
+{
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));  // row_shr:1
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));  // row_bcast:15 into rows 1 and 3
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+__device__ __forceinline__ void bw_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// HS: heads in a slice (a slice lies inside one head: 1).  WMODE: W_LOAD (weights at the edge's own position, or at eid[])
+// or W_ATT_FWD (attention codes computed on the fly, as in k_spmm).
+//
+// The edge streams (indices; weight codes, or the codes of the sources) come from HBM, whose latency would be paid per block,
+// because the wait for a block's gathers waits for everything requested before it.  They are therefore fetched for four
+// blocks at a time, one group of four ahead, and handed on through LDS.
+template <int SW, int HS, int WMODE, bool HAS_EID>
+__global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_spmm_blocks(spmm_args a, bw_grid gs)
+{
+    constexpr int T = SW / 16;  // 16-column tiles of a slice
+    constexpr bool ATT = WMODE == W_ATT_FWD;
+    static_assert(T % HS == 0 && HS <= 4, "a tile lies inside one head, the codes of an edge in a word");
+    __shared__ __align__(16) int8_t tile_s[WAVES_PER_BLOCK][64 * SW];
+    __shared__ __align__(16) uint32_t at_s[WAVES_PER_BLOCK][256];            // rows (or offsets) of the gathered table
+    __shared__ __align__(16) int8_t w_s[WAVES_PER_BLOCK][HS * (ATT ? 64 : 256)];  // weight codes, head-major
+    __shared__ uint32_t code_s[ATT ? WAVES_PER_BLOCK : 1][ATT ? 256 * HS / 4 : 1];  // S_q of the sources, HS bytes per edge
+    __shared__ int row_s[ATT ? WAVES_PER_BLOCK : 1][64];
+    const int lane = threadIdx.x % TANGO_WAVE;
+    const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / TANGO_WAVE));
+    int slice;
+    unsigned group;
+    bw_place(gs, slice, group);
+    const int64_t chunk = static_cast<int64_t>(group) * WAVES_PER_BLOCK + wv;
+    const int64_t c0l = chunk << a.chunk_shift;
+    if (c0l >= a.nnz) return;
+    const int c0 = static_cast<int>(c0l), c1 = static_cast<int>(min(c0l + (int64_t(1) << a.chunk_shift), a.nnz));
+    const int col0 = slice * SW, h0 = col0 / a.dim;
+    const int g = lane >> 4, n16 = lane & 15;
+    const int8_t *X = a.X + col0;
+    int8_t *tile = tile_s[wv];
+    int8_t *wl = w_s[wv];
+    float s_w, inv_w = 0.0f, att_sS = 0.0f, att_sD = 0.0f;
+    if (ATT) {
+        tango_scale_from_absmax(*a.att.absmax_alpha, s_w, inv_w);
+        if (blockIdx.x == 0 && threadIdx.x == 0) *a.att.s_alpha = s_w;
+        att_sS = *a.att.sS;
+        att_sD = *a.att.sD;
+    } else {
+        s_w = *a.s_w;
+    }
+    const float sc = s_w * (*a.s_X);
+    const int H = a.heads;
+
+    // Graph row r is row 4*(r & 3) + ((r >> 2) & 3) of the matrix product: accumulator register i of lane group g then
+    // belongs to the row with r & 15 == 4*i + g, so that four consecutive rows share a register across the lane groups
+    // and a row keeps its place from block to block.
+    const int a_row = ((n16 & 3) << 2) | (n16 >> 2);  // r & 15 of the row whose weights this lane holds
+    bw_v4i acc[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) acc[t] = bw_v4i{0, 0, 0, 0};
+    // transposing reads: lane i of group g reads row 16g + i/2 (and the row 8 further), half i%2 of a 16-byte chunk
+    const int tr_row = 16 * g + (n16 >> 1);
+    const int tr_base = tr_row * SW + (n16 & 1) * 8, tr_swz = bw_swz<SW>(tr_row) * 16;
+    int maxabs = 0;
+
+    int R = c0 == 0 ? 0 : __builtin_amdgcn_readfirstlane(wave_find_row(a.ptr, a.n, c0));  // first row with an edge at or behind the walk
+    auto load_row_ends = [&](int r0, int &lo, int &hi) {  // lane l: where row r0 + l starts and ends (rows beyond the last: nnz)
+        lo = a.ptr[min(r0 + lane, a.n)];
+        hi = a.ptr[min(r0 + lane + 1, a.n)];
+    };
+    const int last = c1 - 1;
+    // the next four blocks' streams: edges beyond the chunk repeat its last one (their weights are zero)
+    int n_idx[4], n_eid[4];
+    uint32_t n_w[4];
+    auto request_idx = [&](int e0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) n_idx[k] = a.idx[min(e0 + 64 * k + lane, last)];
+    };
+    auto request_eid = [&](int e0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) n_eid[k] = a.eid[min(e0 + 64 * k + lane, last)];
+    };
+    auto request_w = [&](int e0) {  // needs n_eid (HAS_EID) or n_idx (attention without the edge-ordered codes)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t e = min(e0 + 64 * k + lane, last);
+            if (!ATT)
+                n_w[k] = bw_load_bytes<HS>(a.w + (HAS_EID ? static_cast<int64_t>(n_eid[k]) : e) * H + h0, a.w_words);
+            else
+                n_w[k] = bw_load_bytes<HS>(a.att.src_codes ? a.att.src_codes + e * H + h0 : a.att.Sq + static_cast<int64_t>(n_idx[k]) * H + h0, true);
+        }
+    };
+    int row_lo, row_hi;
+    load_row_ends(R, row_lo, row_hi);
+    request_idx(c0);
+    if (HAS_EID) request_eid(c0);
+    request_w(c0);
+    if (HAS_EID) request_eid(c0 + 256);
+
+    // Random bits: one generator block serves eight consecutive (edge, head) elements, so one evaluation by all lanes covers
+    // 64 / H consecutive groups of eight edges = 8 / H blocks of 64 edges.
+    const int rng_every = ATT ? 64 * max(1, 8 / H) : 64;
+    uint4 rng_blk = make_uint4(0, 0, 0, 0);
+    int rng_first = 0;  // the edge whose elements begin with lane 0's block
+    // Attention mode: s_D * D_q and row_lse of the row of every lane's edge, for the block [base, end) whose first row is r0 (lo, hi:
+    // where the rows r0 + lane start and end).  A row that goes on filling whole blocks is fetched once.
+    float td[HS], lse[HS];
+    int held = -1;  // the row whose values all lanes hold
+    auto fetch_rows = [&](int base, int end, int r0, int lo, int hi) {
+        int my_row = r0;
+        if (__builtin_amdgcn_readfirstlane(hi) < end) {  // more than one row
+            row_s[wv][lane] = 0;
+            bw_lds_fence();
+            for (int w = r0;;) {
+                const int l = max(lo - base, 0), h = min(hi, end) - base;
+                if (l < h) row_s[wv][l] = w + lane;
+                if (__builtin_amdgcn_readlane(hi, 63) >= end || w + 64 >= a.n) break;
+                w += 64;
+                load_row_ends(w, lo, hi);
+            }
+            bw_lds_fence();
+            my_row = bw_scan_max(row_s[wv][lane]);
+            held = -1;
+        } else if (held == r0) {
+            return;
+        } else {
+            held = r0;
+        }
+        const int64_t at = static_cast<int64_t>(my_row) * H + h0;
+#pragma unroll
+        for (int h = 0; h < HS; ++h) {
+            td[h] = att_sD * static_cast<float>(a.att.Dq[at + h]);
+            lse[h] = a.att.row_lse[at + h];
+        }
+    };
+    if (ATT) fetch_rows(c0, min(c0 + 64, c1), R, row_lo, row_hi);
+
+    for (int base = c0; base < c1; base += 64) {
+        const int cnt = min(64, c1 - base), end = base + cnt;
+        const int quarter = ((base - c0) >> 6) & 3;
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the previous block's reads of LDS are done
+        if (quarter == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                at_s[wv][64 * k + lane] = ATT ? static_cast<uint32_t>(n_idx[k]) * static_cast<uint32_t>(a.F) : static_cast<uint32_t>(n_idx[k]);
+                if (ATT) {
+                    if (HS == 4) code_s[wv][64 * k + lane] = n_w[k];
+                    else if (HS == 2) reinterpret_cast<uint16_t *>(code_s[wv])[64 * k + lane] = static_cast<uint16_t>(n_w[k]);
+                    else reinterpret_cast<uint8_t *>(code_s[wv])[64 * k + lane] = static_cast<uint8_t>(n_w[k]);
+                } else {
+                    const uint32_t w = base + 64 * k + lane < c1 ? n_w[k] : 0u;
+#pragma unroll
+                    for (int h = 0; h < HS; ++h) wl[256 * h + 64 * k + lane] = static_cast<int8_t>(w >> (8 * h));
+                }
+            }
+            bw_lds_fence();
+        }
+        // ---- gather the block
+        bw_gather<SW, ATT>(X, &at_s[wv][64 * quarter], a.F, tile, lane);
+        if (quarter == 0) {
+            request_idx(base + 256);
+            request_w(base + 256);
+            if (HAS_EID) request_eid(base + 512);
+        }
+        // ---- the weight codes of the block, one byte per edge and head
+        if (ATT) {
+            const int64_t i0 = static_cast<int64_t>(base + lane) * H + h0;
+            uint32_t codes;
+            if (HS == 4) codes = code_s[wv][64 * quarter + lane];
+            else if (HS == 2) codes = reinterpret_cast<const uint16_t *>(code_s[wv])[64 * quarter + lane];
+            else codes = reinterpret_cast<const uint8_t *>(code_s[wv])[64 * quarter + lane];
+            uint4 blk = make_uint4(0, 0, 0, 0);
+            if (a.att.rounding == TANGO_SR) {
+                if ((base - c0) % rng_every == 0) {
+                    rng_first = base;
+                    rng_blk = tango_philox_block(a.att.rng, ((static_cast<uint64_t>(base) * static_cast<uint32_t>(H)) >> 3) + static_cast<uint32_t>(lane));
+                }
+                // (the HS elements of an edge lie in one block: their index is a multiple of HS)
+                const int from = ((base + lane - rng_first) * H + h0) >> 3;
+                blk = make_uint4(__shfl(rng_blk.x, from, 64), __shfl(rng_blk.y, from, 64), __shfl(rng_blk.z, from, 64), __shfl(rng_blk.w, from, 64));
+            }
+#pragma unroll
+            for (int h = 0; h < HS; ++h) {
+                bool pos;
+                const float sq = static_cast<float>(static_cast<int8_t>(codes >> (8 * h)));
+                const float ev = tango_attn_score(att_sS * sq, td[h], a.att.slope, pos);
+                const float al = tango_attn_alpha(ev, lse[h]);
+                const int q = a.att.rounding == TANGO_SR
+                                  ? tango_round_clamp<TANGO_SR>(al * inv_w, tango_bits16(blk, static_cast<int>((i0 + h) & 7)))
+                                  : tango_round_clamp<TANGO_RN>(al * inv_w, 0u);
+                if (lane < cnt) {
+                    if (a.att.alpha_dump) a.att.alpha_dump[i0 + h] = al;
+                    if (a.att.alpha_q) a.att.alpha_q[i0 + h] = static_cast<int8_t>(q);
+                }
+                wl[64 * h + lane] = static_cast<int8_t>(lane < cnt ? q : 0);
+            }
+        }
+        bw_lds_fence();
+        bw_v4i wf[HS];  // the codes of edges 16g .. 16g+15
+#pragma unroll
+        for (int h = 0; h < HS; ++h)
+            wf[h] = *reinterpret_cast<const bw_v4i *>(wl + (ATT ? 64 * h : 256 * h + 64 * quarter) + 16 * g);
+        int nrows = __popcll(__ballot(R + lane < a.n && row_lo < end));  // rows of the window with an edge before `end`
+        int nfin = __popcll(__ballot(R + lane < a.n && row_hi <= end));  // and those that end by then
+        int next_lo = row_lo, next_hi = row_hi;
+        if (nfin > 0) load_row_ends(R + nfin, next_lo, next_hi);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed
+        bw_lds_fence();
+        // the rows of the next block: their values are on the way while this block is multiplied
+        const bool more = end < c1, early = nfin < 64;
+        if (ATT && more && early) fetch_rows(end, min(end + 64, c1), R + nfin, next_lo, next_hi);
+        // ---- sixteen rows at a time: multiply, then write out the rows that end here
+        for (;;) {
+            for (int p = 0; p < nrows; p += 16) {
+                bw_v4i wm[HS];
+                const int src = p + ((a_row - R) & 15);  // the window lane of my row (R + p + j with j = (a_row - R) mod 16)
+                if (nrows == 1 && __builtin_amdgcn_readfirstlane(row_lo) <= base) {  // the whole block is row R's
+#pragma unroll
+                    for (int h = 0; h < HS; ++h)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) wm[h][k] = src == 0 ? wf[h][k] : 0;
+                } else {
+                    uint32_t m[4];
+                    const int lo = __shfl(row_lo, src, 64) - base, hi = min(__shfl(row_hi, src, 64) - base, cnt);
+                    bw_range_mask(lo, hi, g, m);
+#pragma unroll
+                    for (int h = 0; h < HS; ++h)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) wm[h][k] = wf[h][k] & static_cast<int>(m[k]);
+                }
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const int8_t *p0 = tile + (tr_base + ((16 * t) ^ tr_swz));
+                    const bw_v2i f0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((bw_lds_v2i *)p0);
+                    const bw_v2i f1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((bw_lds_v2i *)(p0 + 8 * SW));
+                    const bw_v4i f = {f0[0], f0[1], f1[0], f1[1]};
+                    acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wm[t * HS / T], f, acc[t], 0, 0, 0);
+                }
+                if (nfin <= p) continue;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int j = p + ((4 * i + g - R) & 15);  // the window lane of the row in register i
+                    const bool fin = j < nfin;
+                    if (!__any(fin)) continue;
+                    // (only the row that holds the chunk's first edge can have begun before it: it is shared with other chunks)
+                    const int began = __shfl(row_lo, j, 64);  // (by all lanes: a lane shuffle reads active lanes only)
+                    const bool whole = fin && began >= c0;
+                    const int row = R + j;
+                    if (ATT && a.relu_bits) {
+#pragma unroll
+                        for (int t = 0; t < T; ++t) {
+                            const unsigned long long bits = __ballot(acc[t][i] > 0);
+                            if (whole && n16 == 0)
+                                a.relu_bits[(static_cast<uint32_t>(row) * static_cast<uint32_t>(a.F / 16)) + (col0 / 16 + t)] =
+                                    static_cast<uint16_t>(bits >> (16 * g));
+                        }
+                    }
+                    if (fin) {
+                        float *orow = a.out + (static_cast<int64_t>(row) * a.F + col0 + n16);
+                        if (whole) {
+#pragma unroll
+                            for (int t = 0; t < T; ++t) {
+                                int v = acc[t][i];
+                                if (ATT && a.relu) v = max(v, 0);
+                                orow[16 * t] = static_cast<float>(v) * sc;
+                                maxabs = max(maxabs, abs(v));
+                            }
+                        } else {
+#pragma unroll
+                            for (int t = 0; t < T; ++t) atomicAdd(reinterpret_cast<int *>(orow) + 16 * t, acc[t][i]);
+                        }
+#pragma unroll
+                        for (int t = 0; t < T; ++t) acc[t][i] = 0;
+                    }
+                }
+            }
+            R += nfin;
+            row_lo = next_lo;
+            row_hi = next_hi;
+            if (nfin < 64 || R >= a.n || __builtin_amdgcn_readfirstlane(row_lo) >= end) break;
+            nrows = __popcll(__ballot(R + lane < a.n && row_lo < end));  // the window ended inside the block: the next one
+            nfin = __popcll(__ballot(R + lane < a.n && row_hi <= end));
+            load_row_ends(R + nfin, next_lo, next_hi);
+        }
+        if (ATT && more && !early) fetch_rows(end, min(end + 64, c1), R, row_lo, row_hi);
+    }
+    // the row that runs on into the next chunk
+    if (R < a.n) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (((R >> 2) & 3) != i) continue;
+            int *orow = reinterpret_cast<int *>(a.out + (static_cast<int64_t>(R) * a.F + col0 + n16));
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if (g == (R & 3) && acc[t][i] != 0) atomicAdd(orow + 16 * t, acc[t][i]);
+        }
+    }
+    if (a.absmax) {
+        float m = static_cast<float>(maxabs) * sc;
+        m = tango_wave_max(m);
+        if (lane == 0 && m > 0.0f) tango_atomic_max_nonneg(a.absmax, m);
+    }
+}

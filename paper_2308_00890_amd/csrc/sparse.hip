@@ -752,6 +752,8 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
     }
 }
 
+#include "blockwalk.hip.h"
+
 // Short rows (at most a.short_max <= 64 edges), plain weights, small graphs: each group of LPR lanes owns one row and
 // walks its edges alone, so a wave works on G rows at once and a row needs no cross-group reduction, no atomics and no
 // chunk search.  Small low-degree graphs spend most of their edges here; the chunked kernel above then only sees the
@@ -1287,6 +1289,44 @@ int pick_vec_i4(int F, int dim)
     return 0;
 }
 
+// Slice of a feature row that k_spmm_blocks works on: the widest of 128, 64, 32 bytes that divides the row and either lies
+// inside one head or holds up to four whole heads of at least 16 columns; 0: none.
+int pick_slice(int F, int dim)
+{
+    for (int sw = 128; sw >= 32; sw /= 2)
+        if (F % sw == 0 && (dim % sw == 0 || (sw % dim == 0 && dim >= 16 && sw / dim <= 4))) return sw;
+    return 0;
+}
+
+template <int WMODE, bool HAS_EID>
+int launch_spmm_blocks(const spmm_args &a, int sw, hipStream_t st)
+{
+    const int64_t chunks = (a.nnz + (int64_t(1) << a.chunk_shift) - 1) >> a.chunk_shift;
+    bw_grid gs;
+    gs.slices = a.F / sw;
+    gs.groups = static_cast<unsigned>((chunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+    const bool by_xcd = gs.slices == 2 || gs.slices == 4 || gs.slices == 8;
+    const unsigned per = by_xcd ? 8u / gs.slices : 1u;
+    const unsigned blocks = by_xcd ? (gs.groups + per - 1) / per * 8u : gs.groups * static_cast<unsigned>(gs.slices);
+    const int hs = a.dim >= sw ? 1 : sw / a.dim;
+#define TANGO_BLOCKS(SW_, HS_) k_spmm_blocks<SW_, HS_, WMODE, HAS_EID><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a, gs)
+    if (sw == 128) {
+        if (hs == 1) TANGO_BLOCKS(128, 1);
+        else if (hs == 2) TANGO_BLOCKS(128, 2);
+        else TANGO_BLOCKS(128, 4);
+    } else if (sw == 64) {
+        if (hs == 1) TANGO_BLOCKS(64, 1);
+        else if (hs == 2) TANGO_BLOCKS(64, 2);
+        else TANGO_BLOCKS(64, 4);
+    } else {
+        if (hs == 1) TANGO_BLOCKS(32, 1);
+        else TANGO_BLOCKS(32, 2);
+    }
+#undef TANGO_BLOCKS
+    TANGO_LAUNCH_CHECK();
+    return TANGO_OK;
+}
+
 // w_src[j][h] = w[eid[j]][h]: edge codes from destination-major to source-major order.
 __global__ __launch_bounds__(256) void k_edge_to_src_order(int64_t nnz, int heads, const int32_t *__restrict__ eid,
                                                            const int8_t *__restrict__ w, int8_t *__restrict__ w_src)
@@ -1374,7 +1414,11 @@ static int spmm_launch(const tango_graph *g, int direction, int heads, int dim, 
     const bool low_degree = !x4 && !att && a.n > 0 && a.nnz / a.n <= 20;
     int tiny = 0;
     a.short_max = 0;
-    if (low_degree && small_graph && a.F <= 256) a.short_max = 64;
+    // (the attention walk addresses the gathered table with 32 bits)
+    const bool small_table = static_cast<int64_t>(a.n) * a.F < (int64_t(1) << 32);
+    const int sw = (x4 || (att && (direction != TANGO_IN || att->rec || !small_table))) ? 0 : pick_slice(a.F, dim);
+    if (sw) { /* every row length alike */ }
+    else if (low_degree && small_graph && a.F <= 256) a.short_max = 64;
     else if (low_degree && !a.eid && a.F <= 512) a.short_max = tiny = (a.F <= 128 ? 8 : 4);
     // (a wave of the two helper kernels handles the flagged rows of its pass one after the other: where split rows are
     // dense - fewer than 16 rows per chunk boundary, i.e. small graphs and long rows - short passes spread that chain of
@@ -1440,6 +1484,15 @@ static int spmm_launch(const tango_graph *g, int direction, int heads, int dim, 
                     break;
             }
             TANGO_LAUNCH_CHECK();
+            k_spmm_finalize<<<row_blocks, 256, 0, st>>>(a);
+            TANGO_LAUNCH_CHECK();
+            return TANGO_OK;
+        }
+        if (sw) {
+            a.w_words = tango_aligned(w_q, static_cast<size_t>(dim >= sw ? 1 : sw / dim));  // the codes of a slice's heads as one word
+            const int rc = att ? launch_spmm_blocks<W_ATT_FWD, false>(a, sw, st)
+                               : (a.eid ? launch_spmm_blocks<W_LOAD, true>(a, sw, st) : launch_spmm_blocks<W_LOAD, false>(a, sw, st));
+            if (rc != TANGO_OK) return rc;
             k_spmm_finalize<<<row_blocks, 256, 0, st>>>(a);
             TANGO_LAUNCH_CHECK();
             return TANGO_OK;

@@ -120,6 +120,54 @@ def test_qspmm(T, gname, heads, dim, direction):
     assert host(am)[0] == want_am
 
 
+def block_graph():
+    """Rows that meet every edge of a walk in blocks of 64 edges: exactly 64 edges, 1 and 63, hundreds of empty rows inside a
+    block and between blocks, rows of one edge (more than 16 and more than 64 rows in a block), a row over many blocks and
+    chunks, empty rows first and last."""
+    rng = np.random.default_rng(77)
+    n = 2600
+    deg = np.zeros(n, np.int64)
+    deg[3] = 64
+    deg[5], deg[6] = 1, 63
+    deg[200:264] = 1
+    deg[300], deg[301], deg[700] = 31, 33, 30
+    deg[701:720] = 3
+    deg[1000] = 2600
+    deg[1001], deg[1300], deg[1301] = 40, 24, 7
+    deg[1400:1560] = 1
+    deg[1600:1900] = rng.integers(0, 9, 300)
+    deg[2100:2500:7] = 5
+    src = np.concatenate([rng.choice(n, d, replace=False) for d in deg if d])
+    dst = np.repeat(np.arange(n), deg)
+    return ti.graph_from_edges(n, src, dst, self_loops=False)
+
+
+@pytest.mark.parametrize("heads,dim", [(1, 32), (2, 16), (1, 96), (4, 16), (1, 64), (3, 64), (8, 16), (4, 32), (2, 64), (3, 128), (2, 192),
+                                       (1, 1024)])
+@pytest.mark.parametrize("direction,shift", [(0, 0), (0, 1), (1, 0), (2, 3)])
+def test_qspmm_block_walk(T, heads, dim, direction, shift):
+    """The matrix-core aggregation at every slice width and head count of a slice, weights at any byte alignment, against
+    the integer oracle (exact)."""
+    import torch
+
+    g = block_graph()
+    G = T.Graph.from_host(g)
+    F = heads * dim
+    w = rand_i8((g.n_edges, heads), 3)
+    X = rand_i8((g.n_nodes, F), 4)
+    sw, sx = np.float32(1.0 / 127), np.float32(0.0213)
+    wd = w[g.out_eid] if direction == 2 else w
+    buf = empty((wd.size + shift,), torch.int8)
+    buf[shift:] = dev(wd).reshape(-1)
+    out, am = empty((g.n_nodes, F), torch.float32), scalar(-1)
+    out.fill_(float("nan"))
+    T.tango_qspmm(G, direction, heads, dim, buf[shift:], scalar(sw), dev(X), scalar(sx), out, am)
+    torch.cuda.synchronize()
+    want, want_am = (orc.spmm_in if direction == 0 else orc.spmm_rev)(g, w, sw, X, sx)
+    assert_bit_exact(host(out), want, "spmm h%d d%d dir%d" % (heads, dim, direction))
+    assert host(am)[0] == want_am
+
+
 @pytest.mark.parametrize("gname,heads,dim", CASES)
 def test_qsddmm_dot(T, gname, heads, dim):
     import torch
