@@ -28,7 +28,7 @@ int tango_spmm_attention_rev_ds_async(const tango_graph *g, int heads, int dim, 
                                       float *absmax_out, float *dS, bool dS_acc_zeroed, hipStream_t st, bool out_prezeroed = false);
 int tango_attn_bwd_dst_fused_async(const tango_graph *g, int heads, int dim, const int8_t *dOut_q, const float *s_dOut,
                                    const int8_t *X_q, const float *s_X, const int8_t *Sq, const float *sS, const int8_t *Dq,
-                                   const float *sD, float slope, const float *row_lse, double *stats, void *rec,
+                                   const float *sD, float slope, const float *row_lse, unsigned long long *stats, void *rec,
                                    float *dD, const int8_t *src_codes, double *also_zero, bool prezeroed, hipStream_t st);
 int tango_validate_spmm_shape(int heads, int dim);
 int tango_validate_sddmm_dot_shape(int heads, int dim);
@@ -388,7 +388,7 @@ int tango_gat_attention_bwd_dst(const tango_graph *g, int heads, int dim, const 
     TANGO_REQUIRE(ws && tango_aligned(ws, 256) && ws_bytes >= tango_gat_attention_bwd_dst_workspace_bytes(g->n_nodes, heads),
                   TANGO_ERR_WORKSPACE);
     return tango_attn_bwd_dst_fused_async(g, heads, dim, dOut_q, s_dOut, X_q, s_X, S_q, s_S, D_q, s_D, slope, row_lse,
-                                          static_cast<double *>(ws), rec, dD, nullptr, nullptr, false,
+                                          static_cast<unsigned long long *>(ws), rec, dD, nullptr, nullptr, false,
                                           tango_stream(stream));
 }
 
@@ -475,7 +475,7 @@ int tango_gat_attention_bwd_cached(const tango_graph *g, int heads, int dim, con
     const size_t rec_bytes = tango_gat_attention_bwd_rec_bytes(g->n_nodes, heads);
     void *rec = static_cast<char *>(ws) + 256;
     double *dS_acc = reinterpret_cast<double *>(static_cast<char *>(ws) + 256 + rec_bytes);
-    double *stats = reinterpret_cast<double *>(static_cast<char *>(ws) + 256 + rec_bytes + nh_bytes);
+    unsigned long long *stats = reinterpret_cast<unsigned long long *>(static_cast<char *>(ws) + 256 + rec_bytes + nh_bytes);
     int *huge = reinterpret_cast<int *>(static_cast<char *>(ws) + 256 + rec_bytes + 4 * nh_bytes);
     if (edge_part && !alpha_q && !dalpha) {
         // no edge tensor at all: 5'', 4', 3'' in one walk over the in-edges, then 5' and 3' in one walk over the out-edges

@@ -96,3 +96,30 @@ struct __attribute__((aligned(16))) tango_attn_rec {
     int32_t dq;      // the destination's quantized projection D_q[v][h]
 };
 __host__ __device__ static inline int tango_rec_heads(int heads) { return heads <= 1 ? 1 : heads <= 2 ? 2 : heads <= 4 ? 4 : 8; }
+
+// The three sums per (destination, head) of the destination-side backward walk (A = sum alpha*dalpha, B = sum
+// alpha*dalpha*s, C = sum alpha*s) are formed in fp64 inside a wave and meet in memory as 64-bit fixed point: integer
+// addition does not depend on the order in which the waves arrive (dD = B - A*C cancels almost completely where all
+// scores of a row have one sign, and an fp64 sum in another order then shows in the fp32 result).  The grid follows from
+// what the sums can reach: |dalpha| <= scale * dim * 127^2 and a row's alpha add up to 1, so one step of the grid is 2^-60 of that
+// bound, below the last bit of an fp64 sum down to 2^-8 of the bound.
+struct tango_row_sum_grid {
+    int ab, c;  // binary exponents: A and B are stored as A * 2^ab, C as C * 2^c
+};
+__device__ static inline tango_row_sum_grid tango_row_sum_grid_for(float scale, int dim, float slope)
+{
+    const double s = fmax(1.0, fabs(static_cast<double>(slope)));
+    int e_ab, e_c;
+    frexp(fabs(static_cast<double>(scale)) * dim * 16129.0 * s, &e_ab);
+    frexp(1.5 * s, &e_c);
+    return tango_row_sum_grid{60 - e_ab, 60 - e_c};
+}
+__device__ static inline void tango_row_sum_add(unsigned long long *p, double v, int exponent)
+{
+    const long long q = static_cast<long long>(rint(ldexp(v, exponent)));
+    if (q != 0) atomicAdd(p, static_cast<unsigned long long>(q));
+}
+__device__ static inline double tango_row_sum_value(unsigned long long q, int exponent)
+{
+    return ldexp(static_cast<double>(static_cast<long long>(q)), -exponent);
+}

@@ -31,14 +31,15 @@ struct bw_grid {
     unsigned groups;  // workgroups per slice
 };
 
-// Chunk 16 of row r of a block sits in slot chunk ^ bw_swz(r): the 32 lanes of one LDS cycle of a transposing read (eight rows
-// of two groups of sixteen rows, one 16-byte chunk each) then cover all 64 banks once.
+// 16-byte chunk c of row r of a block sits in slot c ^ bw_swz(r).  Both kinds of LDS reads then cover all 64 banks once per
+// cycle: sixteen consecutive rows at one chunk (16-byte reads), and eight rows of each of two groups of sixteen rows at
+// one chunk (transposing reads).  bw_swz(r + 8) == bw_swz(r) ^ (chunks per row / 2) for r % 16 < 8.
 template <int SW>
 __device__ __forceinline__ int bw_swz(int r)
 {
-    if (SW == 128) return ((r >> 1) & 3) | (((r >> 4) & 1) << 2);
-    if (SW == 64) return ((r >> 2) & 1) | (((r >> 4) & 1) << 1);
-    return (r >> 4) & 1;
+    if (SW == 128) return ((r >> 1) & 7) ^ (((r >> 4) & 1) << 2);
+    if (SW == 64) return ((r >> 2) & 3) ^ (((r >> 4) & 1) << 1);
+    return ((r >> 3) & 1) ^ ((r >> 4) & 1);
 }
 
 // Which slice and which group of chunks this workgroup takes.
@@ -83,6 +84,16 @@ __device__ __forceinline__ uint32_t bw_load_bytes(const int8_t *p, bool aligned)
     return w;
 }
 
+// Columns 16t .. 16t+15 of the 64 rows as a matrix operand (k = the rows): lane i of group g reads row 16g + i/2 and the row 8
+// further, half i%2 of the 16-byte chunk; base, swz: that row's place and its swizzle in bytes.
+template <int SW>
+__device__ __forceinline__ bw_v4i bw_columns(const int8_t *tile, int base, int swz, int t)
+{
+    const bw_v2i f0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((bw_lds_v2i *)(tile + (base + ((16 * t) ^ swz))));
+    const bw_v2i f1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((bw_lds_v2i *)(tile + (base + ((16 * (t ^ (SW / 32))) ^ swz)) + 8 * SW));
+    return bw_v4i{f0[0], f0[1], f1[0], f1[1]};
+}
+
 // Byte masks (0xff / 0) of edges 16*kg .. 16*kg+15 of a block that lie in [lo, hi).
 __device__ __forceinline__ void bw_range_mask(int lo, int hi, int kg, uint32_t (&m)[4])
 {
@@ -114,21 +125,22 @@ __device__ __forceinline__ void bw_lds_fence()
 }
 
 // HS: heads in a slice (a slice lies inside one head: 1).  WMODE: W_LOAD (weights at the edge's own position, or at eid[])
-// or W_ATT_FWD (attention codes computed on the fly, as in k_spmm).
+// or W_ATT_FWD (attention codes computed on the fly, as in k_spmm; KEEP: alpha and its codes may be asked for).
 //
 // The edge streams (indices; weight codes, or the codes of the sources) come from HBM, whose latency would be paid per block,
-// because the wait for a block's gathers waits for everything requested before it.  They are therefore fetched for four
-// blocks at a time, one group of four ahead, and handed on through LDS.
-template <int SW, int HS, int WMODE, bool HAS_EID>
-__global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_spmm_blocks(spmm_args a, bw_grid gs)
+// because the wait for a block's gathers waits for everything requested before it.  They are therefore fetched for a group of
+// blocks at a time, one group ahead, and handed on through LDS.
+template <int SW, int HS, int WMODE, bool HAS_EID, bool KEEP = false>
+__global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_per_eu(SW == 128 && HS == 4 && WMODE == W_ATT_FWD ? 3 : 4))) void k_spmm_blocks(spmm_args a, bw_grid gs)
 {
     constexpr int T = SW / 16;  // 16-column tiles of a slice
     constexpr bool ATT = WMODE == W_ATT_FWD;
+    constexpr int GB = ATT && SW == 128 && HS > 1 ? 2 : 4;  // blocks whose streams are fetched together (registers allow only two there)
     static_assert(T % HS == 0 && HS <= 4, "a tile lies inside one head, the codes of an edge in a word");
     __shared__ __align__(16) int8_t tile_s[WAVES_PER_BLOCK][64 * SW];
-    __shared__ __align__(16) uint32_t at_s[WAVES_PER_BLOCK][256];            // rows (or offsets) of the gathered table
-    __shared__ __align__(16) int8_t w_s[WAVES_PER_BLOCK][HS * (ATT ? 64 : 256)];  // weight codes, head-major
-    __shared__ uint32_t code_s[ATT ? WAVES_PER_BLOCK : 1][ATT ? 256 * HS / 4 : 1];  // S_q of the sources, HS bytes per edge
+    __shared__ __align__(16) uint32_t at_s[WAVES_PER_BLOCK][64 * GB];            // rows (or offsets) of the gathered table
+    __shared__ __align__(16) int8_t w_s[WAVES_PER_BLOCK][HS * (ATT ? 64 : 64 * GB)];  // weight codes, head-major
+    __shared__ uint32_t code_s[ATT ? WAVES_PER_BLOCK : 1][ATT ? 64 * GB * HS / 4 : 1];  // S_q of the sources, HS bytes per edge
     __shared__ int row_s[ATT ? WAVES_PER_BLOCK : 1][64];
     const int lane = threadIdx.x % TANGO_WAVE;
     const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / TANGO_WAVE));
@@ -169,30 +181,34 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
     int maxabs = 0;
 
     int R = c0 == 0 ? 0 : __builtin_amdgcn_readfirstlane(wave_find_row(a.ptr, a.n, c0));  // first row with an edge at or behind the walk
-    auto load_row_ends = [&](int r0, int &lo, int &hi) {  // lane l: where row r0 + l starts and ends (rows beyond the last: nnz)
+    auto load_row_ends = [&](int r0, int &lo, int &hi) __attribute__((always_inline)) {  // lane l: where row r0 + l starts and ends (rows beyond the last: nnz)
         lo = a.ptr[min(r0 + lane, a.n)];
         hi = a.ptr[min(r0 + lane + 1, a.n)];
     };
     const int last = c1 - 1;
-    // the next four blocks' streams: edges beyond the chunk repeat its last one (their weights are zero)
-    int n_idx[4], n_eid[4];
-    uint32_t n_w[4];
-    auto request_idx = [&](int e0) {
+    // the next group's streams: edges beyond the chunk repeat its last one (their weights are zero)
+    int n_idx[GB], n_eid[GB];
+    uint32_t n_w[GB];
+    auto request_idx = [&](int e0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) n_idx[k] = a.idx[min(e0 + 64 * k + lane, last)];
+        for (int k = 0; k < GB; ++k) n_idx[k] = a.idx[min(e0 + 64 * k + lane, last)];
     };
-    auto request_eid = [&](int e0) {
+    auto request_eid = [&](int e0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) n_eid[k] = a.eid[min(e0 + 64 * k + lane, last)];
+        for (int k = 0; k < GB; ++k) n_eid[k] = a.eid[min(e0 + 64 * k + lane, last)];
     };
-    auto request_w = [&](int e0) {  // needs n_eid (HAS_EID) or n_idx (attention without the edge-ordered codes)
+    const int8_t *stream = ATT ? a.att.src_codes : (HAS_EID ? nullptr : a.w);  // the codes in edge order, where there are such
+    const bool aligned = ATT || a.w_words;
+    auto request_w = [&](int e0) __attribute__((always_inline)) {
+        if (stream) {  // (a branch of its own: nothing in it waits for the indices)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int64_t e = min(e0 + 64 * k + lane, last);
-            if (!ATT)
-                n_w[k] = bw_load_bytes<HS>(a.w + (HAS_EID ? static_cast<int64_t>(n_eid[k]) : e) * H + h0, a.w_words);
-            else
-                n_w[k] = bw_load_bytes<HS>(a.att.src_codes ? a.att.src_codes + e * H + h0 : a.att.Sq + static_cast<int64_t>(n_idx[k]) * H + h0, true);
+            for (int k = 0; k < GB; ++k) n_w[k] = bw_load_bytes<HS>(stream + static_cast<int64_t>(min(e0 + 64 * k + lane, last)) * H + h0, aligned);
+        } else if (ATT) {
+#pragma unroll
+            for (int k = 0; k < GB; ++k) n_w[k] = bw_load_bytes<HS>(a.att.Sq + static_cast<int64_t>(n_idx[k]) * H + h0, true);
+        } else if (HAS_EID) {
+#pragma unroll
+            for (int k = 0; k < GB; ++k) n_w[k] = bw_load_bytes<HS>(a.w + static_cast<int64_t>(n_eid[k]) * H + h0, aligned);
         }
     };
     int row_lo, row_hi;
@@ -200,18 +216,19 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
     request_idx(c0);
     if (HAS_EID) request_eid(c0);
     request_w(c0);
-    if (HAS_EID) request_eid(c0 + 256);
+    if (HAS_EID) request_eid(c0 + 64 * GB);
 
     // Random bits: one generator block serves eight consecutive (edge, head) elements, so one evaluation by all lanes covers
     // 64 / H consecutive groups of eight edges = 8 / H blocks of 64 edges.
     const int rng_every = ATT ? 64 * max(1, 8 / H) : 64;
     uint4 rng_blk = make_uint4(0, 0, 0, 0);
     int rng_first = 0;  // the edge whose elements begin with lane 0's block
-    // Attention mode: s_D * D_q and row_lse of the row of every lane's edge, for the block [base, end) whose first row is r0 (lo, hi:
+    // Attention mode: D_q and row_lse of the row of every lane's edge, for the block [base, end) whose first row is r0 (lo, hi:
     // where the rows r0 + lane start and end).  A row that goes on filling whole blocks is fetched once.
-    float td[HS], lse[HS];
+    uint32_t dq = 0;  // (as loaded: nothing here waits for the loads)
+    float lse[HS];
     int held = -1;  // the row whose values all lanes hold
-    auto fetch_rows = [&](int base, int end, int r0, int lo, int hi) {
+    auto fetch_rows = [&](int base, int end, int r0, int lo, int hi) __attribute__((always_inline)) {
         int my_row = r0;
         if (__builtin_amdgcn_readfirstlane(hi) < end) {  // more than one row
             row_s[wv][lane] = 0;
@@ -232,21 +249,19 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
             held = r0;
         }
         const int64_t at = static_cast<int64_t>(my_row) * H + h0;
+        dq = bw_load_bytes<HS>(a.att.Dq + at, true);
 #pragma unroll
-        for (int h = 0; h < HS; ++h) {
-            td[h] = att_sD * static_cast<float>(a.att.Dq[at + h]);
-            lse[h] = a.att.row_lse[at + h];
-        }
+        for (int h = 0; h < HS; ++h) lse[h] = a.att.row_lse[at + h];
     };
     if (ATT) fetch_rows(c0, min(c0 + 64, c1), R, row_lo, row_hi);
 
     for (int base = c0; base < c1; base += 64) {
         const int cnt = min(64, c1 - base), end = base + cnt;
-        const int quarter = ((base - c0) >> 6) & 3;
+        const int part = ((base - c0) >> 6) & (GB - 1);  // this block's place in its group
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the previous block's reads of LDS are done
-        if (quarter == 0) {
+        if (part == 0) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < GB; ++k) {
                 at_s[wv][64 * k + lane] = ATT ? static_cast<uint32_t>(n_idx[k]) * static_cast<uint32_t>(a.F) : static_cast<uint32_t>(n_idx[k]);
                 if (ATT) {
                     if (HS == 4) code_s[wv][64 * k + lane] = n_w[k];
@@ -255,25 +270,25 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
                 } else {
                     const uint32_t w = base + 64 * k + lane < c1 ? n_w[k] : 0u;
 #pragma unroll
-                    for (int h = 0; h < HS; ++h) wl[256 * h + 64 * k + lane] = static_cast<int8_t>(w >> (8 * h));
+                    for (int h = 0; h < HS; ++h) wl[64 * GB * h + 64 * k + lane] = static_cast<int8_t>(w >> (8 * h));
                 }
             }
             bw_lds_fence();
         }
         // ---- gather the block
-        bw_gather<SW, ATT>(X, &at_s[wv][64 * quarter], a.F, tile, lane);
-        if (quarter == 0) {
-            request_idx(base + 256);
-            request_w(base + 256);
-            if (HAS_EID) request_eid(base + 512);
+        bw_gather<SW, ATT>(X, &at_s[wv][64 * part], a.F, tile, lane);
+        if (part == 0) {
+            request_idx(base + 64 * GB);
+            request_w(base + 64 * GB);
+            if (HAS_EID) request_eid(base + 128 * GB);
         }
         // ---- the weight codes of the block, one byte per edge and head
         if (ATT) {
             const int64_t i0 = static_cast<int64_t>(base + lane) * H + h0;
             uint32_t codes;
-            if (HS == 4) codes = code_s[wv][64 * quarter + lane];
-            else if (HS == 2) codes = reinterpret_cast<const uint16_t *>(code_s[wv])[64 * quarter + lane];
-            else codes = reinterpret_cast<const uint8_t *>(code_s[wv])[64 * quarter + lane];
+            if (HS == 4) codes = code_s[wv][64 * part + lane];
+            else if (HS == 2) codes = reinterpret_cast<const uint16_t *>(code_s[wv])[64 * part + lane];
+            else codes = reinterpret_cast<const uint8_t *>(code_s[wv])[64 * part + lane];
             uint4 blk = make_uint4(0, 0, 0, 0);
             if (a.att.rounding == TANGO_SR) {
                 if ((base - c0) % rng_every == 0) {
@@ -288,12 +303,13 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
             for (int h = 0; h < HS; ++h) {
                 bool pos;
                 const float sq = static_cast<float>(static_cast<int8_t>(codes >> (8 * h)));
-                const float ev = tango_attn_score(att_sS * sq, td[h], a.att.slope, pos);
+                const float td = att_sD * static_cast<float>(static_cast<int8_t>(dq >> (8 * h)));
+                const float ev = tango_attn_score(att_sS * sq, td, a.att.slope, pos);
                 const float al = tango_attn_alpha(ev, lse[h]);
                 const int q = a.att.rounding == TANGO_SR
                                   ? tango_round_clamp<TANGO_SR>(al * inv_w, tango_bits16(blk, static_cast<int>((i0 + h) & 7)))
                                   : tango_round_clamp<TANGO_RN>(al * inv_w, 0u);
-                if (lane < cnt) {
+                if (KEEP && lane < cnt) {
                     if (a.att.alpha_dump) a.att.alpha_dump[i0 + h] = al;
                     if (a.att.alpha_q) a.att.alpha_q[i0 + h] = static_cast<int8_t>(q);
                 }
@@ -304,7 +320,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
         bw_v4i wf[HS];  // the codes of edges 16g .. 16g+15
 #pragma unroll
         for (int h = 0; h < HS; ++h)
-            wf[h] = *reinterpret_cast<const bw_v4i *>(wl + (ATT ? 64 * h : 256 * h + 64 * quarter) + 16 * g);
+            wf[h] = *reinterpret_cast<const bw_v4i *>(wl + (ATT ? 64 * h : 64 * GB * h + 64 * part) + 16 * g);
         int nrows = __popcll(__ballot(R + lane < a.n && row_lo < end));  // rows of the window with an edge before `end`
         int nfin = __popcll(__ballot(R + lane < a.n && row_hi <= end));  // and those that end by then
         int next_lo = row_lo, next_hi = row_hi;
@@ -335,10 +351,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
                 }
 #pragma unroll
                 for (int t = 0; t < T; ++t) {
-                    const int8_t *p0 = tile + (tr_base + ((16 * t) ^ tr_swz));
-                    const bw_v2i f0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((bw_lds_v2i *)p0);
-                    const bw_v2i f1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((bw_lds_v2i *)(p0 + 8 * SW));
-                    const bw_v4i f = {f0[0], f0[1], f1[0], f1[1]};
+                    const bw_v4i f = bw_columns<SW>(tile, tr_base, tr_swz, t);
                     acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wm[t * HS / T], f, acc[t], 0, 0, 0);
                 }
                 if (nfin <= p) continue;
@@ -405,4 +418,324 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
         m = tango_wave_max(m);
         if (lane == 0 && m > 0.0f) tango_atomic_max_nonneg(a.absmax, m);
     }
+}
+
+// Dot products over blocks of 64 edges: for every edge of a block and every head of a slice (whole heads: HS of them, at most
+// 128 columns) the product of the gathered row with the resident row of the edge's own graph row.  DOT_STORE writes them out;
+// DOT_DST (steps 5'', 4', 3'': see k_sddmm_dot) turns them into the three running sums per (row, head).
+//
+// The gathered rows (LDS, as in k_spmm_blocks) are the left operand of v_mfma_i32_16x16x64_i8, sixteen edges at a time, k =
+// their columns.  The right operand has sixteen columns: column 4q + c is the resident row number c of the rows that the
+// sixteen edges 16q .. 16q+15 belong to.  Lane (group g, column 4q + c) then finds the products of edges 16q + 4g + i,
+// i = 0..3, with that row in its four result registers of step q; the one that belongs to the edge's row is picked with a
+// sum over the four lanes of a quad, and lane (g, 4q + c) goes on with edge 16q + 4g + c: no trip through LDS.  Edges whose
+// group of sixteen spans more than four rows take further rounds of four rows.
+template <int SW, int HS, int MODE>
+__global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_dot_blocks(sddmm_dot_args a, bw_grid gs)
+{
+    constexpr bool ATT = MODE == DOT_DST;
+    constexpr int GB = ATT && SW == 128 ? 2 : 4;  // blocks whose streams are fetched together
+    constexpr int NC = SW >= 64 ? SW / 64 : 1;   // 64-column steps of a slice
+    constexpr int DIM = SW / HS;                 // columns of a head
+    constexpr int HPC = DIM >= 64 ? 1 : (SW >= 64 ? 64 : SW) / DIM;  // heads in a 64-column step
+    __shared__ __align__(16) int8_t tile_s[WAVES_PER_BLOCK][64 * SW];
+    __shared__ __align__(16) uint32_t at_s[WAVES_PER_BLOCK][64 * GB];
+    __shared__ uint32_t code_s[ATT ? WAVES_PER_BLOCK : 1][ATT ? 64 * GB * HS / 4 : 1];
+    __shared__ __align__(16) int row_s[WAVES_PER_BLOCK][64];
+    __shared__ __align__(16) float2 val_s[ATT ? WAVES_PER_BLOCK : 1][ATT ? HS : 1][64];  // per head and edge: alpha (negative: the slope side), dalpha
+    const int lane = threadIdx.x % TANGO_WAVE;
+    const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / TANGO_WAVE));
+    int slice;
+    unsigned group;
+    bw_place(gs, slice, group);
+    const int64_t chunk = static_cast<int64_t>(group) * WAVES_PER_BLOCK + wv;
+    const int64_t c0l = chunk << a.chunk_shift;
+    if (c0l >= a.nnz) return;
+    const int c0 = static_cast<int>(c0l), c1 = static_cast<int>(min(c0l + (int64_t(1) << a.chunk_shift), a.nnz)), last = c1 - 1;
+    const int col0 = slice * SW, h0 = slice * HS, H = a.heads;
+    const int g = lane >> 4, n16 = lane & 15, q_l = n16 >> 2, c_l = n16 & 3;
+    const int my_edge = 16 * q_l + 4 * g + c_l;  // the edge of a block that this lane goes on with
+    const int8_t *X = a.Xsrc + col0, *Y = a.Xdst + col0;
+    int8_t *tile = tile_s[wv];
+    const float sc = (*a.s_dst) * (*a.s_src);
+    float sS = 0.0f, sD = 0.0f;
+    tango_row_sum_grid grid{0, 0};
+    if (ATT) {
+        sS = *a.sS;
+        sD = *a.sD;
+        grid = tango_row_sum_grid_for(sc, DIM, a.slope);
+    }
+    int R = c0 == 0 ? 0 : __builtin_amdgcn_readfirstlane(wave_find_row(a.ptr, a.n, c0));
+    auto load_row_ends = [&](int r0, int &lo, int &hi) __attribute__((always_inline)) {
+        lo = a.ptr[min(r0 + lane, a.n)];
+        hi = a.ptr[min(r0 + lane + 1, a.n)];
+    };
+    int n_idx[GB];
+    uint32_t n_w[GB];
+    auto request = [&](int e0) __attribute__((always_inline)) {  // the next group's streams
+#pragma unroll
+        for (int k = 0; k < GB; ++k) n_idx[k] = a.idx[min(e0 + 64 * k + lane, last)];
+        if (ATT && a.src_codes) {  // (a branch of its own: nothing in it waits for the indices)
+#pragma unroll
+            for (int k = 0; k < GB; ++k) n_w[k] = bw_load_bytes<HS>(a.src_codes + static_cast<int64_t>(min(e0 + 64 * k + lane, last)) * H + h0, true);
+        } else if (ATT) {
+#pragma unroll
+            for (int k = 0; k < GB; ++k) n_w[k] = bw_load_bytes<HS>(a.Sq + static_cast<int64_t>(n_idx[k]) * H + h0, true);
+        }
+    };
+    auto hand_over = [&]() __attribute__((always_inline)) {  // ... and into LDS
+#pragma unroll
+        for (int k = 0; k < GB; ++k) {
+            at_s[wv][64 * k + lane] = static_cast<uint32_t>(n_idx[k]) * static_cast<uint32_t>(a.F);
+            if (ATT) {
+                if (HS == 4) code_s[wv][64 * k + lane] = n_w[k];
+                else if (HS == 2) reinterpret_cast<uint16_t *>(code_s[wv])[64 * k + lane] = static_cast<uint16_t>(n_w[k]);
+                else reinterpret_cast<uint8_t *>(code_s[wv])[64 * k + lane] = static_cast<uint8_t>(n_w[k]);
+            }
+        }
+        bw_lds_fence();
+    };
+    // What a block needs of its graph rows: `held` >= 0: one row for the whole block, else row_s holds every edge's row.  The
+    // resident rows of round 0 of the products, and D_q and row_lse of the row of this lane's edge, are requested.
+    int held = -1, spans = 0;  // spans: the most rows a group of sixteen edges lies in, less one
+    bw_v4i resident[NC];
+    uint32_t dq = 0, dq_n = 0;  // D_q and row_lse of the row of this lane's edge (as loaded: nothing here waits for the loads)
+    float lse[HS], lse_n[HS];
+    auto load_resident = [&](int row) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            resident[k] = bw_v4i{0, 0, 0, 0};
+            if (SW >= 64 || g < 2) resident[k] = *reinterpret_cast<const bw_v4i *>(Y + static_cast<int64_t>(row) * a.F + 64 * k + 16 * g);
+        }
+    };
+    auto fetch_rows = [&](int base, int end, int r0, int lo, int hi) __attribute__((always_inline)) {
+        int my_row = r0;
+        if (__builtin_amdgcn_readfirstlane(hi) < end) {
+            row_s[wv][lane] = 0;
+            bw_lds_fence();
+            for (int w = r0;;) {
+                const int l = max(lo - base, 0), h = min(hi, end) - base;
+                if (l < h) row_s[wv][l] = w + lane;
+                if (__builtin_amdgcn_readlane(hi, 63) >= end || w + 64 >= a.n) break;
+                w += 64;
+                load_row_ends(w, lo, hi);
+            }
+            bw_lds_fence();
+            const int row_of = bw_scan_max(row_s[wv][lane]);
+            row_s[wv][lane] = row_of;  // (edges beyond the block: the last row)
+            bw_lds_fence();
+            my_row = row_s[wv][my_edge];
+            const int first = row_s[wv][16 * q_l], final = row_s[wv][16 * q_l + 15];
+            held = -1;
+            spans = 0;
+            for (int d = 4; __any(final - first >= d); d += 4) spans = d;
+            load_resident(min(first + c_l, final));
+        } else if (held == r0) {
+            dq_n = dq;
+#pragma unroll
+            for (int h = 0; h < HS; ++h) lse_n[h] = lse[h];
+            return;
+        } else {
+            held = r0;
+            spans = 0;
+            load_resident(r0);
+        }
+        if (ATT) {
+            const int64_t at = static_cast<int64_t>(my_row) * H + h0;
+            dq_n = bw_load_bytes<HS>(a.Dq + at, true);
+#pragma unroll
+            for (int h = 0; h < HS; ++h) lse_n[h] = a.row_lse[at + h];
+        }
+    };
+    int row_lo, row_hi;
+    load_row_ends(R, row_lo, row_hi);
+    request(c0);
+    fetch_rows(c0, min(c0 + 64, c1), R, row_lo, row_hi);
+    hand_over();
+    bw_gather<SW, true>(X, &at_s[wv][0], a.F, tile, lane);
+    request(c0 + 64 * GB);
+    double acc[HS][3];  // the sums of the row that fills whole blocks
+    int acc_row = -1;
+#pragma unroll
+    for (int h = 0; h < HS; ++h) acc[h][0] = acc[h][1] = acc[h][2] = 0.0;
+    auto flush = [&]() __attribute__((always_inline)) {
+        if (acc_row < 0) return;
+#pragma unroll
+        for (int h = 0; h < HS; ++h) {
+            const double t0 = tango_stride_sum_f64(acc[h][0], 1), t1 = tango_stride_sum_f64(acc[h][1], 1), t2 = tango_stride_sum_f64(acc[h][2], 1);
+            const double t = lane == 0 ? t0 : (lane == 1 ? t1 : t2);
+            if (lane < 3) tango_row_sum_add(a.stats + (static_cast<int64_t>(acc_row) * H + h0 + h) * 3 + lane, t, lane == 2 ? grid.c : grid.ab);
+            acc[h][0] = acc[h][1] = acc[h][2] = 0.0;
+        }
+        acc_row = -1;
+    };
+
+    for (int base = c0; base < c1; base += 64) {
+        const int cnt = min(64, c1 - base), end = base + cnt;
+        const int place = ((base - c0) >> 6) & (GB - 1);  // this block's place in its group
+        const int nrows = __popcll(__ballot(R + lane < a.n && row_lo < end));
+        const int nfin = __popcll(__ballot(R + lane < a.n && row_hi <= end));
+        int next_lo = row_lo, next_hi = row_hi;
+        if (nfin > 0) load_row_ends(R + nfin, next_lo, next_hi);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed
+        bw_lds_fence();
+        // ---- the dot products of my edge, all heads
+        const bool uniform = held >= 0;
+        const int block_row = held;
+        int dot[HS];
+#pragma unroll
+        for (int h = 0; h < HS; ++h) {
+            dot[h] = 0;
+            lse[h] = lse_n[h];
+        }
+        dq = dq_n;
+        int4 rows4 = make_int4(0, 0, 0, 0);
+        int first = 0, final = 0;
+        if (!uniform) {
+            rows4 = *reinterpret_cast<const int4 *>(&row_s[wv][16 * q_l + 4 * g]);
+            first = row_s[wv][16 * q_l];
+            final = row_s[wv][16 * q_l + 15];
+        }
+        for (int d0 = 0; d0 <= spans; d0 += 4) {
+            if (d0 > 0) load_resident(min(first + d0 + c_l, final));
+#pragma unroll
+            for (int h = 0; h < HS; ++h) {
+                bw_v4i res[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) res[q] = bw_v4i{0, 0, 0, 0};
+                constexpr int KH = DIM >= 64 ? DIM / 64 : 1;  // steps of a head
+#pragma unroll
+                for (int k = 0; k < KH; ++k) {
+                    const int kc = DIM >= 64 ? h * KH + k : h / HPC;
+                    bw_v4i b = resident[kc];
+                    if (HPC > 1) {  // several heads in the 64 columns: zero the others
+                        const bool mine = (16 * g) / DIM == h % HPC;
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) b[w] = mine ? b[w] : 0;
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int r = 16 * q + n16;
+                        bw_v4i f = {0, 0, 0, 0};
+                        if (SW >= 64 || g < 2) f = *reinterpret_cast<const bw_v4i *>(tile + r * SW + (((4 * kc + g) ^ bw_swz<SW>(r)) * 16));
+                        res[q] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f, b, res[q], 0, 0, 0);
+                    }
+                }
+                int v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = q_l == 0 ? res[0][i] : (q_l == 1 ? res[1][i] : (q_l == 2 ? res[2][i] : res[3][i]));
+                if (!uniform) {
+                    const int row = first + d0 + c_l;
+                    v[0] = rows4.x == row ? v[0] : 0;
+                    v[1] = rows4.y == row ? v[1] : 0;
+                    v[2] = rows4.z == row ? v[2] : 0;
+                    v[3] = rows4.w == row ? v[3] : 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = tango_group_sum_c<4>(v[i], 4);
+                }
+                dot[h] += c_l == 0 ? v[0] : (c_l == 1 ? v[1] : (c_l == 2 ? v[2] : v[3]));
+            }
+        }
+        uint32_t codes = 0;
+        if (ATT) {
+            if (HS == 4) codes = code_s[wv][64 * place + my_edge];
+            else if (HS == 2) codes = reinterpret_cast<const uint16_t *>(code_s[wv])[64 * place + my_edge];
+            else codes = reinterpret_cast<const uint8_t *>(code_s[wv])[64 * place + my_edge];
+        }
+        // ---- the next block's gathers, while this one's products are turned into sums
+        const int R_now = R, rows_now = nrows, lo_now = row_lo, hi_now = row_hi;
+        bool wide = nfin == 64 && nrows == 64;  // (the window of 64 rows may end inside the block)
+        R += nfin;
+        row_lo = next_lo;
+        row_hi = next_hi;
+        while (wide && R < a.n && __builtin_amdgcn_readfirstlane(row_lo) < end) {
+            const int more = __popcll(__ballot(R + lane < a.n && row_hi <= end));
+            R += more;
+            wide = more == 64;
+            load_row_ends(R, row_lo, row_hi);
+        }
+        if (end < c1) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this block's reads of LDS are done
+            if (place == GB - 1) hand_over();
+            fetch_rows(end, min(end + 64, c1), R, row_lo, row_hi);
+            bw_gather<SW, true>(X, &at_s[wv][64 * ((place + 1) & (GB - 1))], a.F, tile, lane);
+            if (place == GB - 1) request(end + 64 * GB);
+        }
+        const bool there = my_edge < cnt;
+        if (!ATT) {
+            if (there) {
+                float *o = a.out + (static_cast<int64_t>(base) + my_edge) * H + h0;
+#pragma unroll
+                for (int h = 0; h < HS; ++h) o[h] = static_cast<float>(dot[h]) * sc;
+            }
+            continue;
+        }
+        if (uniform && acc_row != block_row) {
+            flush();
+            acc_row = block_row;
+        }
+#pragma unroll
+        for (int h = 0; h < HS; ++h) {
+            const float da = static_cast<float>(dot[h]) * sc;
+            bool pos;
+            const float td = sD * static_cast<float>(static_cast<int8_t>(dq >> (8 * h)));
+            const float ev = tango_attn_score(sS * static_cast<float>(static_cast<int8_t>(codes >> (8 * h))), td, a.slope, pos);
+            float al = tango_attn_alpha(ev, lse[h]);
+            if (uniform) {
+                al = there ? al : 0.0f;
+                const double sl = pos ? 1.0 : static_cast<double>(a.slope);
+                const double ad = static_cast<double>(al) * static_cast<double>(da);
+                acc[h][0] += ad;
+                acc[h][1] += ad * sl;
+                acc[h][2] += static_cast<double>(al) * sl;
+            } else {
+                val_s[wv][h][my_edge] = make_float2(pos ? al : -al, da);
+            }
+        }
+        if (!uniform) {
+            flush();
+            // a group of P lanes per (row of the block, head): they share the row's edges
+            bw_lds_fence();
+            int w = R_now, nr = rows_now, lo = lo_now, hi = hi_now;
+            for (;;) {
+                const int items = nr * HS;
+                const int log2P = items <= 4 ? 4 : (items <= 8 ? 3 : (items <= 16 ? 2 : (items <= 32 ? 1 : 0)));
+                const int P = 1 << log2P, part = lane & (P - 1);
+                for (int it0 = 0; it0 < items; it0 += 64 >> log2P) {
+                    const int it = it0 + (lane >> log2P);
+                    const int j = min(it / HS, 63), h = it % HS;
+                    const int row_b = __shfl(lo, j, 64), row_t = __shfl(hi, j, 64);  // (by all lanes: a shuffle reads active lanes only)
+                    const int b = max(row_b - base, 0), t = it < items ? min(row_t - base, cnt) : 0;
+                    double sa = 0.0, sb = 0.0, sc3 = 0.0;
+#pragma unroll 4
+                    for (int e = b + part; e < t; e += P) {
+                        const float2 v = val_s[wv][h][e];
+                        const double sl = __float_as_int(v.x) >= 0 ? 1.0 : static_cast<double>(a.slope);
+                        const double al = static_cast<double>(fabsf(v.x));
+                        const double ad = al * static_cast<double>(v.y);
+                        sa += ad;
+                        sb += ad * sl;
+                        sc3 += al * sl;
+                    }
+                    sa = tango_group_sum_f64(sa, P);
+                    sb = tango_group_sum_f64(sb, P);
+                    sc3 = tango_group_sum_f64(sc3, P);
+                    if (b < t) {
+                        unsigned long long *st = a.stats + (static_cast<int64_t>(w + j) * H + h0 + h) * 3;
+                        for (int k = part; k < 3; k += P) {
+                            const double v = k == 0 ? sa : (k == 1 ? sb : sc3);
+                            tango_row_sum_add(st + k, v, k == 2 ? grid.c : grid.ab);
+                        }
+                    }
+                }
+                if (nr < 64 || w + 64 >= a.n) break;
+                w += 64;
+                load_row_ends(w, lo, hi);
+                nr = __popcll(__ballot(w + lane < a.n && lo < end));
+                if (nr == 0) break;
+            }
+            bw_lds_fence();
+        }
+    }
+    if (ATT) flush();
 }

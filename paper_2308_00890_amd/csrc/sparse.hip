@@ -752,8 +752,6 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
     }
 }
 
-#include "blockwalk.hip.h"
-
 // Short rows (at most a.short_max <= 64 edges), plain weights, small graphs: each group of LPR lanes owns one row and
 // walks its edges alone, so a wave works on G rows at once and a row needs no cross-group reduction, no atomics and no
 // chunk search.  Small low-degree graphs spend most of their edges here; the chunked kernel above then only sees the
@@ -1018,10 +1016,12 @@ struct sddmm_dot_args {
     const float *row_lse;            // n x heads
     int chunk_shift = CHUNK_SHIFT_DEFAULT;  // log2 of the edges per wavefront
     const int8_t *src_codes = nullptr;  // optional: S_q[src(e)] per in-edge, in edge order (read instead of gathered)
-    double *stats;                   // n x heads x 3, zero-initialised: sum alpha*dalpha, sum alpha*dalpha*s, sum alpha*s
+    unsigned long long *stats;       // n x heads x 3, zero-initialised: sum alpha*dalpha, sum alpha*dalpha*s, sum alpha*s (tango_row_sum_grid)
 };
 
 enum { DOT_STORE = 0, DOT_SRC = 1, DOT_DST = 2 };
+
+#include "blockwalk.hip.h"
 
 // out[e][h] = (float)(Xdst[dst(e)][h][:] . Xsrc[src(e)][h][:]) * (s_dst*s_src); one wave per chunk of edges.
 // ATT_BWD (step 3' fused with 5'', 4' and LeakyReLU', walking the out-edges of each source u): the dot product
@@ -1075,9 +1075,11 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_sddmm_dot(sddmm_dot_ar
     const int ekstep = S / HP;
     const bool ep_on = lane < S && eh < H;
     float sS = 0.0f, sD = 0.0f;
+    tango_row_sum_grid grid{0, 0};
     if (ATT_BWD || ATT_DST) {
         sS = *a.sS;
         sD = *a.sD;
+        if (ATT_DST) grid = tango_row_sum_grid_for(sc, a.dim, a.slope);
     }
 
     // the blocks of a chunk follow each other in the edge array whatever rows they belong to, so the neighbour indices
@@ -1219,7 +1221,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_sddmm_dot(sddmm_dot_ar
             const int w = lane / HP;  // lane = HP*(which sum) + head
             if (w < 3 && eh < H) {
                 const double t = w == 0 ? ta : (w == 1 ? tb : tc);
-                if (t != 0.0) atomicAdd(a.stats + (static_cast<int64_t>(r) * H + eh) * 3 + w, t);
+                tango_row_sum_add(a.stats + (static_cast<int64_t>(r) * H + eh) * 3 + w, t, w == 2 ? grid.c : grid.ab);
             }
         }
         if (ATT_BWD) {
@@ -1250,6 +1252,9 @@ bool is_pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
 // SDDMM-dot: 256 edges per wavefront, 64 on graphs too small to give every SIMD a few such chunks (a wave walks its
 // rows one after the other, so on a small graph the longest chain of rows sets the time)
 int dot_chunk_shift(int64_t nnz) { return (nnz >> CHUNK_SHIFT_DEFAULT) >= 4096 ? CHUNK_SHIFT_DEFAULT : 6; }
+
+// The same for the SPMM and for the walks in blocks of 64 edges: 1,024 edges where that leaves 16 waves per SIMD, else 256 or 64.
+int block_chunk_shift(int64_t nnz) { return (nnz >> 10) >= 16384 ? 10 : ((nnz >> 8) >= 4096 ? 8 : 6); }
 
 // Bytes of a feature row per lane: aim at ~16 lanes per row.  Every lane's bytes must stay inside one
 // head, the lanes of one row must fit a wave, and the number of row groups per wave must be a power
@@ -1298,18 +1303,72 @@ int pick_slice(int F, int dim)
     return 0;
 }
 
-template <int WMODE, bool HAS_EID>
+// The workgroups of a walk over nnz edges in chunks of 2^shift, `slices` slices of a row each (see bw_place); their number.
+unsigned bw_grid_for(int64_t nnz, int shift, int slices, bw_grid &gs)
+{
+    const int64_t chunks = (nnz + (int64_t(1) << shift) - 1) >> shift;
+    gs.slices = slices;
+    gs.groups = static_cast<unsigned>((chunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+    const bool by_xcd = slices == 2 || slices == 4 || slices == 8;
+    const unsigned per = by_xcd ? 8u / slices : 1u;
+    return by_xcd ? (gs.groups + per - 1) / per * 8u : gs.groups * static_cast<unsigned>(slices);
+}
+
+// Slice of a row that k_dot_blocks works on: the widest of 128, 64, 32 bytes that divides the row and holds one to four whole
+// heads of at least 16 columns; 0: none (or a table beyond 32-bit offsets), or the walk with a lane group per row
+// (k_sddmm_dot) is the faster one.  That walk reads a row's neighbours without a matrix operand to build, so it gains with the
+// row length and with every further head, which costs the block walk an epilogue per (edge, head).  Measured over R-MAT
+// graphs of 6 M edges, lane groups against blocks in us, at mean degree 17, 40 and 100 -
+//   storing:          1x64 163:63, 97:52, 61:43    2x128 220:178, 140:132, 101:114   4x64 237:226, 141:151, 103:131
+//   attention sums:   1x64 377:126, 231:100, 149:80   2x64 422:208, 257:165, 166:138   3x128 587:431, 345:301, 240:252
+//                     4x32 399:326, 255:252, 165:206   4x64 444:428, 260:313, 165:258   8x32 521:667
+int pick_dot_slice(int64_t n, int64_t nnz, int heads, int dim, bool attention)
+{
+    const int F = heads * dim;
+    if (n * F >= (int64_t(1) << 32)) return 0;
+    const int64_t degree = n > 0 ? nnz / n : 0;
+    if (heads > 4) return 0;
+    if (F > 128 || heads > 2) {
+        if (degree > (heads <= 3 ? 64 : (F <= 128 ? 40 : 20))) return 0;
+    } else if (!attention && heads == 2 && degree > 200) {
+        return 0;
+    }
+    for (int sw = 128; sw >= 32; sw /= 2)
+        if (F % sw == 0 && sw % dim == 0 && dim >= 16 && sw / dim <= 4) return sw;
+    return 0;
+}
+
+template <int MODE>
+int launch_dot_blocks(const sddmm_dot_args &a, int sw, hipStream_t st)
+{
+    bw_grid gs;
+    const unsigned blocks = bw_grid_for(a.nnz, a.chunk_shift, a.F / sw, gs);
+    const int hs = sw / a.dim;
+#define TANGO_DOT(SW_, HS_) k_dot_blocks<SW_, HS_, MODE><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a, gs)
+    if (sw == 128) {
+        if (hs == 1) TANGO_DOT(128, 1);
+        else if (hs == 2) TANGO_DOT(128, 2);
+        else TANGO_DOT(128, 4);
+    } else if (sw == 64) {
+        if (hs == 1) TANGO_DOT(64, 1);
+        else if (hs == 2) TANGO_DOT(64, 2);
+        else TANGO_DOT(64, 4);
+    } else {
+        if (hs == 1) TANGO_DOT(32, 1);
+        else TANGO_DOT(32, 2);
+    }
+#undef TANGO_DOT
+    TANGO_LAUNCH_CHECK();
+    return TANGO_OK;
+}
+
+template <int WMODE, bool HAS_EID, bool KEEP = false>
 int launch_spmm_blocks(const spmm_args &a, int sw, hipStream_t st)
 {
-    const int64_t chunks = (a.nnz + (int64_t(1) << a.chunk_shift) - 1) >> a.chunk_shift;
     bw_grid gs;
-    gs.slices = a.F / sw;
-    gs.groups = static_cast<unsigned>((chunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
-    const bool by_xcd = gs.slices == 2 || gs.slices == 4 || gs.slices == 8;
-    const unsigned per = by_xcd ? 8u / gs.slices : 1u;
-    const unsigned blocks = by_xcd ? (gs.groups + per - 1) / per * 8u : gs.groups * static_cast<unsigned>(gs.slices);
+    const unsigned blocks = bw_grid_for(a.nnz, a.chunk_shift, a.F / sw, gs);
     const int hs = a.dim >= sw ? 1 : sw / a.dim;
-#define TANGO_BLOCKS(SW_, HS_) k_spmm_blocks<SW_, HS_, WMODE, HAS_EID><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a, gs)
+#define TANGO_BLOCKS(SW_, HS_) k_spmm_blocks<SW_, HS_, WMODE, HAS_EID, KEEP><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a, gs)
     if (sw == 128) {
         if (hs == 1) TANGO_BLOCKS(128, 1);
         else if (hs == 2) TANGO_BLOCKS(128, 2);
@@ -1401,9 +1460,7 @@ static int spmm_launch(const tango_graph *g, int direction, int heads, int dim, 
     a.F = heads * dim;
     // edges per wavefront: large chunks mean fewer rows cut by a boundary (fewer atomics); small graphs
     // need small chunks to fill 256 CUs
-    a.chunk_shift = 6;
-    if ((a.nnz >> 10) >= 16384) a.chunk_shift = 10;  // at least 16 waves per SIMD worth of chunks
-    else if ((a.nnz >> 8) >= 4096) a.chunk_shift = 8;
+    a.chunk_shift = block_chunk_shift(a.nnz);
     // Low mean degree, plain weights.  Small graphs (too few rows to fill the chip with 64-row passes), either
     // direction, rows of at most two cache lines: rows of up to 64 edges go to the group-per-row kernel (measured: 3-20 %
     // faster there).  Large graphs, weights at the edge's own position: the tiny rows (the self-loop and a few
@@ -1416,7 +1473,12 @@ static int spmm_launch(const tango_graph *g, int direction, int heads, int dim, 
     a.short_max = 0;
     // (the attention walk addresses the gathered table with 32 bits)
     const bool small_table = static_cast<int64_t>(a.n) * a.F < (int64_t(1) << 32);
-    const int sw = (x4 || (att && (direction != TANGO_IN || att->rec || !small_table))) ? 0 : pick_slice(a.F, dim);
+    int sw = (x4 || (att && (direction != TANGO_IN || att->rec || !small_table))) ? 0 : pick_slice(a.F, dim);
+    // Rows of several slices from a table that one L2 holds anyway: the slices buy nothing there, and with long rows (or weights
+    // fetched through the edge-id map once per slice) the walk that reads whole rows is the faster one.  Measured over R-MAT
+    // graphs of 6 M edges, lane groups against blocks in us: 4 x 64 at mean degree 100 147:129, at 250 114:118, at 600 103:110;
+    // through the edge-id map 3 x 128 at 40 376:367, at 100 273:287, at 250 234:263.
+    if (!att && a.F > sw && static_cast<int64_t>(a.n) * a.F <= (int64_t(16) << 20) && a.nnz / a.n >= (a.eid ? 64 : 200)) sw = 0;
     if (sw) { /* every row length alike */ }
     else if (low_degree && small_graph && a.F <= 256) a.short_max = 64;
     else if (low_degree && !a.eid && a.F <= 512) a.short_max = tiny = (a.F <= 128 ? 8 : 4);
@@ -1490,7 +1552,8 @@ static int spmm_launch(const tango_graph *g, int direction, int heads, int dim, 
         }
         if (sw) {
             a.w_words = tango_aligned(w_q, static_cast<size_t>(dim >= sw ? 1 : sw / dim));  // the codes of a slice's heads as one word
-            const int rc = att ? launch_spmm_blocks<W_ATT_FWD, false>(a, sw, st)
+            const int rc = att ? (att->alpha_q || att->alpha_dump ? launch_spmm_blocks<W_ATT_FWD, false, true>(a, sw, st)
+                                                                   : launch_spmm_blocks<W_ATT_FWD, false>(a, sw, st))
                                : (a.eid ? launch_spmm_blocks<W_LOAD, true>(a, sw, st) : launch_spmm_blocks<W_LOAD, false>(a, sw, st));
             if (rc != TANGO_OK) return rc;
             k_spmm_finalize<<<row_blocks, 256, 0, st>>>(a);
@@ -1592,8 +1655,12 @@ int tango_sddmm_dot_async(const tango_graph *g, int heads, int dim, const int8_t
     a.heads = heads;
     a.dim = dim;
     a.F = heads * dim;
+    if (const int sw = pick_dot_slice(a.n, a.nnz, heads, dim, false)) {
+        a.chunk_shift = block_chunk_shift(a.nnz);
+        return launch_dot_blocks<DOT_STORE>(a, sw, st);
+    }
     a.chunk_shift = dot_chunk_shift(a.nnz);
-        const int64_t chunks = (a.nnz + (int64_t(1) << a.chunk_shift) - 1) >> a.chunk_shift;
+    const int64_t chunks = (a.nnz + (int64_t(1) << a.chunk_shift) - 1) >> a.chunk_shift;
     const unsigned blocks = static_cast<unsigned>((chunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
     switch (pick_vec(a.F, dim, true, true)) {
         case 4: k_sddmm_dot<4, DOT_STORE><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a); break;
@@ -1608,13 +1675,16 @@ int tango_sddmm_dot_async(const tango_graph *g, int heads, int dim, const int8_t
     return TANGO_OK;
 }
 
-__global__ __launch_bounds__(256) void k_attn_dst_finish(int64_t nh, int heads, const double *__restrict__ stats, const float *__restrict__ row_lse,
+__global__ __launch_bounds__(256) void k_attn_dst_finish(int64_t nh, int heads, int dim, const unsigned long long *__restrict__ stats,
+                                                         const float *s_dst, const float *s_src, float slope, const float *__restrict__ row_lse,
                                                          const int8_t *__restrict__ Dq,
                                                          void *__restrict__ rec, float *__restrict__ dD)
 {
+    const tango_row_sum_grid grid = tango_row_sum_grid_for((*s_dst) * (*s_src), dim, slope);
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < nh;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const double A = stats[3 * i], B = stats[3 * i + 1], C = stats[3 * i + 2];
+        const double A = tango_row_sum_value(stats[3 * i], grid.ab), B = tango_row_sum_value(stats[3 * i + 1], grid.ab),
+                     C = tango_row_sum_value(stats[3 * i + 2], grid.c);
         const int64_t node = i / heads;
         const int h = static_cast<int>(i - node * heads);
         tango_attn_rec rc;
@@ -1630,7 +1700,7 @@ __global__ __launch_bounds__(256) void k_attn_dst_finish(int64_t nh, int heads, 
 // doubles of scratch.
 int tango_attn_bwd_dst_fused_async(const tango_graph *g, int heads, int dim, const int8_t *dOut_q, const float *s_dOut,
                                    const int8_t *X_q, const float *s_X, const int8_t *Sq, const float *sS, const int8_t *Dq,
-                                   const float *sD, float slope, const float *row_lse, double *stats, void *rec,
+                                   const float *sD, float slope, const float *row_lse, unsigned long long *stats, void *rec,
                                    float *dD, const int8_t *src_codes, double *also_zero, bool prezeroed, hipStream_t st)
 {
     // also_zero (may be NULL): n x heads more doubles zeroed by the same launch (the source-side pass's accumulator);
@@ -1658,21 +1728,27 @@ int tango_attn_bwd_dst_fused_async(const tango_graph *g, int heads, int dim, con
         a.Sq = Sq; a.Dq = Dq; a.sS = sS; a.sD = sD; a.slope = slope;
         a.rec = nullptr; a.dS_acc = nullptr;
         a.row_lse = row_lse; a.stats = stats; a.src_codes = src_codes;
-        a.chunk_shift = dot_chunk_shift(a.nnz);
-        const int64_t chunks = (a.nnz + (int64_t(1) << a.chunk_shift) - 1) >> a.chunk_shift;
-        const unsigned blocks = static_cast<unsigned>((chunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
-        switch (pick_vec(a.F, dim, true)) {
-            case 4: k_sddmm_dot<4, DOT_DST><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a); break;
-            case 8: k_sddmm_dot<8, DOT_DST><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a); break;
-            default:
-            if (a.dim == 64) k_sddmm_dot<16, DOT_DST, false, 4><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a);
-            else if (a.dim == 128) k_sddmm_dot<16, DOT_DST, false, 8><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a);
-            else k_sddmm_dot<16, DOT_DST><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a);
-            break;
+        if (const int sw = pick_dot_slice(a.n, a.nnz, heads, dim, true)) {
+            a.chunk_shift = block_chunk_shift(a.nnz);
+            const int rc = launch_dot_blocks<DOT_DST>(a, sw, st);
+            if (rc != TANGO_OK) return rc;
+        } else {
+            a.chunk_shift = dot_chunk_shift(a.nnz);
+            const int64_t chunks = (a.nnz + (int64_t(1) << a.chunk_shift) - 1) >> a.chunk_shift;
+            const unsigned blocks = static_cast<unsigned>((chunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+            switch (pick_vec(a.F, dim, true)) {
+                case 4: k_sddmm_dot<4, DOT_DST><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a); break;
+                case 8: k_sddmm_dot<8, DOT_DST><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a); break;
+                default:
+                    if (a.dim == 64) k_sddmm_dot<16, DOT_DST, false, 4><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a);
+                    else if (a.dim == 128) k_sddmm_dot<16, DOT_DST, false, 8><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a);
+                    else k_sddmm_dot<16, DOT_DST><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a);
+                    break;
+            }
+            TANGO_LAUNCH_CHECK();
         }
-        TANGO_LAUNCH_CHECK();
     }
-    k_attn_dst_finish<<<tango_grid_for(static_cast<size_t>(nh), 256), 256, 0, st>>>(nh, heads, stats, row_lse, Dq, rec, dD);
+    k_attn_dst_finish<<<tango_grid_for(static_cast<size_t>(nh), 256), 256, 0, st>>>(nh, heads, dim, stats, s_dOut, s_X, slope, row_lse, Dq, rec, dD);
     TANGO_LAUNCH_CHECK();
     return TANGO_OK;
 }

@@ -52,6 +52,8 @@ def graph(name):
             g = ti.graph_from_edges(37, [], [], self_loops=False)
         elif name == "one":
             g = ti.graph_from_edges(1, [], [], self_loops=True)
+        elif name == "blocks":
+            g = block_graph()
         else:
             raise KeyError(name)
         _graphs[name] = g
@@ -140,6 +142,24 @@ def block_graph():
     src = np.concatenate([rng.choice(n, d, replace=False) for d in deg if d])
     dst = np.repeat(np.arange(n), deg)
     return ti.graph_from_edges(n, src, dst, self_loops=False)
+
+
+@pytest.mark.parametrize("heads,dim", [(1, 32), (2, 16), (3, 32), (4, 16), (1, 64), (2, 32), (3, 64), (4, 32), (2, 64), (1, 128), (3, 128), (4, 64)])
+def test_sddmm_dot_block_walk(T, heads, dim):
+    """The matrix-core dot products at every slice width and head count of a slice, where groups of sixteen edges lie in one,
+    two and many rows, against the integer oracle (exact)."""
+    import torch
+
+    g = block_graph()
+    G = T.Graph.from_host(g)
+    F = heads * dim
+    X, Y = rand_i8((g.n_nodes, F), 5), rand_i8((g.n_nodes, F), 6)
+    sx, sy = np.float32(0.0213), np.float32(0.004)
+    E = empty((g.n_edges, heads), torch.float32)
+    E.fill_(float("nan"))
+    T.tango_qsddmm(G, T.SDDMM_DOT, heads, dim, dev(X), scalar(sx), dev(Y), scalar(sy), 0.0, E)
+    torch.cuda.synchronize()
+    assert_bit_exact(host(E), orc.sddmm_dot(g, Y, sy, X, sx, heads), "sddmm dot h%d d%d" % (heads, dim))
 
 
 @pytest.mark.parametrize("heads,dim", [(1, 32), (2, 16), (1, 96), (4, 16), (1, 64), (3, 64), (8, 16), (4, 32), (2, 64), (3, 128), (2, 192),
