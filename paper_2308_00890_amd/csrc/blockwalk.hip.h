@@ -57,8 +57,9 @@ __device__ __forceinline__ void bw_place(const bw_grid &gs, int &slice, unsigned
 }
 
 // The 64 row slices of a block into LDS; at: LDS, the table rows of the block's edges (rows of F bytes, X: the slice of row
-// 0), as row numbers or, SMALL (the table is known to end below 4 GB), as byte offsets.
-template <int SW, bool SMALL>
+// 0), as row numbers; for a table known to end below 4 GB as byte offsets (BW_OFFSETS), or as row numbers below 2^24 (BW_ROWS24).
+enum { BW_ROWS = 0, BW_OFFSETS = 1, BW_ROWS24 = 2 };
+template <int SW, int KIND>
 __device__ __forceinline__ void bw_gather(const int8_t *__restrict__ X, const uint32_t *at, int F, int8_t *tile, int lane)
 {
     constexpr int CPR = SW / 16, RPI = 64 / CPR;  // chunks of a row slice, rows per load instruction
@@ -67,7 +68,9 @@ __device__ __forceinline__ void bw_gather(const int8_t *__restrict__ X, const ui
     for (int j = 0; j < CPR; ++j) {
         const int r = RPI * j + rr;
         const uint32_t chunk = static_cast<uint32_t>((slot ^ bw_swz<SW>(r)) * 16);
-        const int8_t *from = SMALL ? X + (at[r] + chunk) : X + chunk + static_cast<uint64_t>(at[r]) * static_cast<uint32_t>(F);
+        const int8_t *from = KIND == BW_OFFSETS ? X + (at[r] + chunk)
+                             : KIND == BW_ROWS24 ? X + (__umul24(at[r], static_cast<uint32_t>(F)) + chunk)
+                                                 : X + chunk + static_cast<uint64_t>(at[r]) * static_cast<uint32_t>(F);
         __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t *>(from), reinterpret_cast<uint32_t *>(tile + 1024 * j), 16, 0, 0);
     }
 }
@@ -276,7 +279,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
             bw_lds_fence();
         }
         // ---- gather the block
-        bw_gather<SW, ATT>(X, &at_s[wv][64 * part], a.F, tile, lane);
+        bw_gather<SW, ATT ? BW_OFFSETS : BW_ROWS>(X, &at_s[wv][64 * part], a.F, tile, lane);
         if (part == 0) {
             request_idx(base + 64 * GB);
             request_w(base + 64 * GB);
@@ -552,7 +555,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
     request(c0);
     fetch_rows(c0, min(c0 + 64, c1), R, row_lo, row_hi);
     hand_over();
-    bw_gather<SW, true>(X, &at_s[wv][0], a.F, tile, lane);
+    bw_gather<SW, BW_OFFSETS>(X, &at_s[wv][0], a.F, tile, lane);
     request(c0 + 64 * GB);
     double acc[HS][3];  // the sums of the row that fills whole blocks
     int acc_row = -1;
@@ -658,7 +661,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this block's reads of LDS are done
             if (place == GB - 1) hand_over();
             fetch_rows(end, min(end + 64, c1), R, row_lo, row_hi);
-            bw_gather<SW, true>(X, &at_s[wv][64 * ((place + 1) & (GB - 1))], a.F, tile, lane);
+            bw_gather<SW, BW_OFFSETS>(X, &at_s[wv][64 * ((place + 1) & (GB - 1))], a.F, tile, lane);
             if (place == GB - 1) request(end + 64 * GB);
         }
         const bool there = my_edge < cnt;
@@ -738,4 +741,368 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_p
         }
     }
     if (ATT) flush();
+}
+
+// The source-side walk of the attention backward (steps 5' and 3' in one walk over the out-edges, see the DS form of k_spmm) over
+// blocks of 64 edges.  A block's gathered gradient rows are used twice from LDS: transposed, with the recomputed int8 attention
+// codes, for the aggregation (as in k_spmm_blocks), and as they are, with the resident feature rows, for dalpha of every edge (as
+// in k_dot_blocks).  Lane (g, 4q + c) goes through the attention arithmetic of edge 16q + 4g + c from the codes to dE.
+// What bounds it is the arithmetic per (edge, head) - rounding bits that no other edge shares, score, exp, fp64 difference - and
+// the two random reads of an edge (a row slice and its records): the walk over whole rows spent most of its time in lane-group
+// sums of the dot products and in waits for four rows in flight, here 64 are.  Measured: 1,024 nodes, 16 K edges, 2 x 32: 17.5 ->
+// 8.0 us; 262 K nodes, 4.5 M edges, 2 x 32: 300 -> 136 us; 40 M edges at mean degree 17, 1 x 128: 4.01 -> 1.50 ms, 2 x 64: 4.13 -> 1.63 ms.
+template <int SW, int HS>
+__global__ __launch_bounds__(64 * WAVES_PER_BLOCK) __attribute__((amdgpu_waves_per_eu(SW == 128 ? 3 : 4))) void k_rev_blocks(spmm_args a, bw_grid gs)
+{
+    constexpr int T = SW / 16;
+    constexpr int NC = SW >= 64 ? SW / 64 : 1;
+    constexpr int DIM = SW / HS;
+    constexpr int HPC = DIM >= 64 ? 1 : (SW >= 64 ? 64 : SW) / DIM;
+    constexpr int GB = 2;  // blocks whose streams are fetched together
+    __shared__ __align__(16) int8_t tile_s[WAVES_PER_BLOCK][64 * SW];
+    __shared__ __align__(16) uint32_t at_s[WAVES_PER_BLOCK][64 * GB];
+    __shared__ __align__(16) int8_t w_s[WAVES_PER_BLOCK][HS * 64];
+    __shared__ __align__(16) int row_s[WAVES_PER_BLOCK][64];
+    __shared__ float val_s[WAVES_PER_BLOCK][HS][64];
+    int lane = threadIdx.x % TANGO_WAVE;
+    const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / TANGO_WAVE));
+    int slice;
+    unsigned group;
+    bw_place(gs, slice, group);
+    const int64_t chunk = static_cast<int64_t>(group) * WAVES_PER_BLOCK + wv;
+    const int64_t c0l = chunk << a.chunk_shift;
+    if (c0l >= a.nnz) return;
+    const int c0 = static_cast<int>(c0l), c1 = static_cast<int>(min(c0l + (int64_t(1) << a.chunk_shift), a.nnz)), last = c1 - 1;
+    const int col0 = slice * SW, h0 = slice * HS, H = a.heads;
+    // (what follows from the lane is formed anew for every block, behind an asm that hides the lane from the compiler: hoisted out
+    // of the loop the LDS addresses alone are more registers than there are)
+    int g, n16, q_l, c_l, my_edge, a_row, tr_base, tr_swz;
+    auto from_lane = [&]() __attribute__((always_inline)) {
+        asm volatile("" : "+v"(lane));
+        g = lane >> 4;
+        n16 = lane & 15;
+        q_l = n16 >> 2;
+        c_l = n16 & 3;
+        my_edge = 16 * q_l + 4 * g + c_l;
+        a_row = ((n16 & 3) << 2) | (n16 >> 2);  // r & 15 of the row whose weights this lane holds (see k_spmm_blocks)
+        const int tr_row = 16 * g + (n16 >> 1);
+        tr_base = tr_row * SW + (n16 & 1) * 8;
+        tr_swz = bw_swz<SW>(tr_row) * 16;
+    };
+    from_lane();
+    const int8_t *X = a.X + col0, *Y = a.att.Xrow + col0;
+    int8_t *tile = tile_s[wv];
+    int8_t *wl = w_s[wv];
+    float s_w, inv_w;
+    tango_scale_from_absmax(*a.att.absmax_alpha, s_w, inv_w);
+    const float sS = *a.att.sS, sD = *a.att.sD;
+    const float sc = s_w * (*a.s_X), sc_dot = (*a.s_X) * (*a.att.s_Xrow);
+    const int HP = tango_rec_heads(H);
+    const tango_attn_rec *recs = static_cast<const tango_attn_rec *>(a.att.rec) + h0;
+
+    bw_v4i acc[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) acc[t] = bw_v4i{0, 0, 0, 0};
+    int maxabs = 0;
+
+    int R = c0 == 0 ? 0 : __builtin_amdgcn_readfirstlane(wave_find_row(a.ptr, a.n, c0));
+    auto load_row_ends = [&](int r0, int &lo, int &hi) __attribute__((always_inline)) {
+        lo = a.ptr[min(r0 + lane, a.n)];
+        hi = a.ptr[min(r0 + lane + 1, a.n)];
+    };
+    int n_idx[GB], n_eid[GB], c_eid[GB];
+    auto request = [&](int e0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < GB; ++k) {
+            n_idx[k] = a.idx[min(e0 + 64 * k + lane, last)];
+            n_eid[k] = a.eid[min(e0 + 64 * k + my_edge, last)];
+        }
+    };
+    auto hand_over = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < GB; ++k) {
+            at_s[wv][64 * k + lane] = static_cast<uint32_t>(n_idx[k]);
+            c_eid[k] = n_eid[k];
+        }
+        bw_lds_fence();
+    };
+    int held = -1, spans = 0;  // as in k_dot_blocks
+    bw_v4i resident[NC];
+    uint32_t sq = 0, sq_n = 0;  // S_q of the row of this lane's edge
+    bw_v4i rec_n[HS];           // the records of its neighbour
+    auto load_resident = [&](int row) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            resident[k] = bw_v4i{0, 0, 0, 0};
+            if (SW >= 64 || g < 2) resident[k] = *reinterpret_cast<const bw_v4i *>(Y + static_cast<int64_t>(row) * a.F + 64 * k + 16 * g);
+        }
+    };
+    auto fetch_rows = [&](int base, int end, int r0, int lo, int hi, int place) __attribute__((always_inline)) {
+        const int64_t v = at_s[wv][64 * place + my_edge];
+#pragma unroll
+        for (int h = 0; h < HS; ++h) rec_n[h] = *reinterpret_cast<const bw_v4i *>(recs + v * HP + h);
+        int my_row = r0;
+        if (__builtin_amdgcn_readfirstlane(hi) < end) {
+            row_s[wv][lane] = 0;
+            bw_lds_fence();
+            for (int w = r0;;) {
+                const int l = max(lo - base, 0), h = min(hi, end) - base;
+                if (l < h) row_s[wv][l] = w + lane;
+                if (__builtin_amdgcn_readlane(hi, 63) >= end || w + 64 >= a.n) break;
+                w += 64;
+                load_row_ends(w, lo, hi);
+            }
+            bw_lds_fence();
+            const int row_of = bw_scan_max(row_s[wv][lane]);
+            row_s[wv][lane] = row_of;
+            bw_lds_fence();
+            my_row = row_s[wv][my_edge];
+            const int first = row_s[wv][16 * q_l], final = row_s[wv][16 * q_l + 15];
+            held = -1;
+            spans = 0;
+            for (int d = 4; __any(final - first >= d); d += 4) spans = d;
+            load_resident(min(first + c_l, final));
+        } else if (held == r0) {
+            sq_n = sq;
+            return;
+        } else {
+            held = r0;
+            spans = 0;
+            load_resident(r0);
+        }
+        sq_n = bw_load_bytes<HS>(a.att.Sq + static_cast<int64_t>(my_row) * H + h0, true);
+    };
+    int row_lo, row_hi;
+    load_row_ends(R, row_lo, row_hi);
+    request(c0);
+    hand_over();
+    fetch_rows(c0, min(c0 + 64, c1), R, row_lo, row_hi, 0);
+    bw_gather<SW, BW_ROWS24>(X, &at_s[wv][0], a.F, tile, lane);
+    request(c0 + 64 * GB);
+    double run[HS];  // dS of the row that fills whole blocks
+    int run_row = -1;
+#pragma unroll
+    for (int h = 0; h < HS; ++h) run[h] = 0.0;
+    auto flush_dS = [&]() __attribute__((always_inline)) {
+        if (run_row < 0) return;
+#pragma unroll
+        for (int h = 0; h < HS; ++h) {
+            const double t = tango_stride_sum_f64(run[h], 1);
+            if (lane == 0 && t != 0.0) atomicAdd(a.att.dS_acc + static_cast<int64_t>(run_row) * H + h0 + h, t);
+            run[h] = 0.0;
+        }
+        run_row = -1;
+    };
+
+    for (int base = c0; base < c1; base += 64) {
+        from_lane();
+        const int cnt = min(64, c1 - base), end = base + cnt;
+        const int place = ((base - c0) >> 6) & (GB - 1);
+        const bool uniform = held >= 0, there = my_edge < cnt;
+        const int block_row = held;
+        sq = sq_n;
+        // ---- the attention codes of my edge
+        double P[HS];
+        float al[HS];  // the sign bit says "score not positive"
+        {
+            const int64_t i0 = static_cast<int64_t>(place == 0 ? c_eid[0] : c_eid[1]) * H + h0;
+            uint4 blk = make_uint4(0, 0, 0, 0);
+            if (a.att.rounding == TANGO_SR) blk = tango_philox_block(a.att.rng, static_cast<uint64_t>(i0) >> 3);  // (i0 is a multiple of HS)
+#pragma unroll
+            for (int h = 0; h < HS; ++h) {
+                P[h] = __hiloint2double(rec_n[h][1], rec_n[h][0]);
+                bool pos;
+                const float ev = tango_attn_score(sS * static_cast<float>(static_cast<int8_t>(sq >> (8 * h))), sD * static_cast<float>(rec_n[h][3]),
+                                                  a.att.slope, pos);
+                const float alpha = tango_attn_alpha(ev, __int_as_float(rec_n[h][2]));
+                al[h] = pos ? alpha : -alpha;
+                const int q = a.att.rounding == TANGO_SR
+                                  ? tango_round_clamp<TANGO_SR>(alpha * inv_w, tango_bits16(blk, static_cast<int>((i0 + h) & 7)))
+                                  : tango_round_clamp<TANGO_RN>(alpha * inv_w, 0u);
+                wl[64 * h + my_edge] = static_cast<int8_t>(there ? q : 0);
+            }
+        }
+        int nrows = __popcll(__ballot(R + lane < a.n && row_lo < end));
+        int nfin = __popcll(__ballot(R + lane < a.n && row_hi <= end));
+        const int R_now = R, rows_now = nrows, lo_now = row_lo, hi_now = row_hi;
+        int next_lo = row_lo, next_hi = row_hi;
+        if (nfin > 0) load_row_ends(R + nfin, next_lo, next_hi);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed
+        bw_lds_fence();
+        // ---- dalpha of my edge (see k_dot_blocks)
+        int dot[HS];
+#pragma unroll
+        for (int h = 0; h < HS; ++h) dot[h] = 0;
+        int4 rows4 = make_int4(0, 0, 0, 0);
+        int first = 0, final = 0;
+        if (!uniform) {
+            rows4 = *reinterpret_cast<const int4 *>(&row_s[wv][16 * q_l + 4 * g]);
+            first = row_s[wv][16 * q_l];
+            final = row_s[wv][16 * q_l + 15];
+        }
+        for (int d0 = 0; d0 <= spans; d0 += 4) {
+            if (d0 > 0) load_resident(min(first + d0 + c_l, final));
+#pragma unroll
+            for (int h = 0; h < HS; ++h) {
+                bw_v4i res[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) res[q] = bw_v4i{0, 0, 0, 0};
+                constexpr int KH = DIM >= 64 ? DIM / 64 : 1;
+#pragma unroll
+                for (int k = 0; k < KH; ++k) {
+                    const int kc = DIM >= 64 ? h * KH + k : h / HPC;
+                    bw_v4i b = resident[kc];
+                    if (HPC > 1) {
+                        const bool mine = (16 * g) / DIM == h % HPC;
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) b[w] = mine ? b[w] : 0;
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int r = 16 * q + n16;
+                        bw_v4i f = {0, 0, 0, 0};
+                        if (SW >= 64 || g < 2) f = *reinterpret_cast<const bw_v4i *>(tile + r * SW + (((4 * kc + g) ^ bw_swz<SW>(r)) * 16));
+                        res[q] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f, b, res[q], 0, 0, 0);
+                    }
+                }
+                int v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = q_l == 0 ? res[0][i] : (q_l == 1 ? res[1][i] : (q_l == 2 ? res[2][i] : res[3][i]));
+                if (!uniform) {
+                    const int row = first + d0 + c_l;
+                    v[0] = rows4.x == row ? v[0] : 0;
+                    v[1] = rows4.y == row ? v[1] : 0;
+                    v[2] = rows4.z == row ? v[2] : 0;
+                    v[3] = rows4.w == row ? v[3] : 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = tango_group_sum_c<4>(v[i], 4);
+                }
+                dot[h] += c_l == 0 ? v[0] : (c_l == 1 ? v[1] : (c_l == 2 ? v[2] : v[3]));
+            }
+        }
+        // ---- step 4', LeakyReLU' and step 3' for my edge
+        if (uniform && run_row != block_row) {
+            flush_dS();
+            run_row = block_row;
+        }
+#pragma unroll
+        for (int h = 0; h < HS; ++h) {
+            const float da = static_cast<float>(dot[h]) * sc_dot;
+            const float dE = static_cast<float>(static_cast<double>(fabsf(al[h])) * (static_cast<double>(da) - P[h]));
+            const float d = dE * (__float_as_int(al[h]) < 0 ? a.att.slope : 1.0f);
+            if (uniform) run[h] += there ? static_cast<double>(d) : 0.0;
+            else val_s[wv][h][my_edge] = d;
+        }
+        // ---- the aggregation (see k_spmm_blocks)
+        bw_v4i wf[HS];
+#pragma unroll
+        for (int h = 0; h < HS; ++h) wf[h] = *reinterpret_cast<const bw_v4i *>(wl + 64 * h + 16 * g);
+        for (;;) {
+            for (int p = 0; p < nrows; p += 16) {
+                bw_v4i wm[HS];
+                const int src = p + ((a_row - R) & 15);
+                if (nrows == 1 && __builtin_amdgcn_readfirstlane(row_lo) <= base) {
+#pragma unroll
+                    for (int h = 0; h < HS; ++h)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) wm[h][k] = src == 0 ? wf[h][k] : 0;
+                } else {
+                    uint32_t m[4];
+                    const int lo = __shfl(row_lo, src, 64) - base, hi = min(__shfl(row_hi, src, 64) - base, cnt);
+                    bw_range_mask(lo, hi, g, m);
+#pragma unroll
+                    for (int h = 0; h < HS; ++h)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) wm[h][k] = wf[h][k] & static_cast<int>(m[k]);
+                }
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const bw_v4i f = bw_columns<SW>(tile, tr_base, tr_swz, t);
+                    acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wm[t * HS / T], f, acc[t], 0, 0, 0);
+                }
+                if (nfin <= p) continue;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int j = p + ((4 * i + g - R) & 15);
+                    const bool fin = j < nfin;
+                    if (!__any(fin)) continue;
+                    const int began = __shfl(row_lo, j, 64);
+                    if (fin) {
+                        float *orow = a.out + (static_cast<int64_t>(R + j) * a.F + col0 + n16);
+                        if (began >= c0) {
+#pragma unroll
+                            for (int t = 0; t < T; ++t) {
+                                orow[16 * t] = static_cast<float>(acc[t][i]) * sc;
+                                maxabs = max(maxabs, abs(acc[t][i]));
+                            }
+                        } else {
+#pragma unroll
+                            for (int t = 0; t < T; ++t) atomicAdd(reinterpret_cast<int *>(orow) + 16 * t, acc[t][i]);
+                        }
+#pragma unroll
+                        for (int t = 0; t < T; ++t) acc[t][i] = 0;
+                    }
+                }
+            }
+            R += nfin;
+            row_lo = next_lo;
+            row_hi = next_hi;
+            if (nfin < 64 || R >= a.n || __builtin_amdgcn_readfirstlane(row_lo) >= end) break;
+            nrows = __popcll(__ballot(R + lane < a.n && row_lo < end));
+            nfin = __popcll(__ballot(R + lane < a.n && row_hi <= end));
+            load_row_ends(R + nfin, next_lo, next_hi);
+        }
+        // ---- the next block
+        if (end < c1) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this block's reads of LDS are done
+            if (place == GB - 1) hand_over();
+            fetch_rows(end, min(end + 64, c1), R, row_lo, row_hi, (place + 1) & (GB - 1));
+            bw_gather<SW, BW_ROWS24>(X, &at_s[wv][64 * ((place + 1) & (GB - 1))], a.F, tile, lane);
+            if (place == GB - 1) request(end + 64 * GB);
+        }
+        // ---- step 3' of a block of several rows, while the next gathers are on their way
+        if (!uniform) {
+            flush_dS();
+            bw_lds_fence();
+            int w = R_now, nr = rows_now, lo = lo_now, hi = hi_now;
+            for (;;) {
+                const int items = nr * HS;
+                const int log2P = items <= 4 ? 4 : (items <= 8 ? 3 : (items <= 16 ? 2 : (items <= 32 ? 1 : 0)));
+                const int Pn = 1 << log2P, part = lane & (Pn - 1);
+                for (int it0 = 0; it0 < items; it0 += 64 >> log2P) {
+                    const int it = it0 + (lane >> log2P);
+                    const int j = min(it / HS, 63), h = it % HS;
+                    const int row_b = __shfl(lo, j, 64), row_t = __shfl(hi, j, 64);
+                    const int b = max(row_b - base, 0), t = it < items ? min(row_t - base, cnt) : 0;
+                    double sum = 0.0;
+#pragma unroll 4
+                    for (int e = b + part; e < t; e += Pn) sum += static_cast<double>(val_s[wv][h][e]);
+                    sum = tango_group_sum_f64(sum, Pn);
+                    if (b < t && part == 0 && sum != 0.0) atomicAdd(a.att.dS_acc + static_cast<int64_t>(w + j) * H + h0 + h, sum);
+                }
+                if (nr < 64 || w + 64 >= a.n) break;
+                w += 64;
+                load_row_ends(w, lo, hi);
+                nr = __popcll(__ballot(w + lane < a.n && lo < end));
+                if (nr == 0) break;
+            }
+            bw_lds_fence();
+        }
+    }
+    flush_dS();
+    if (R < a.n) {  // the row that runs on into the next chunk
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (((R >> 2) & 3) != i) continue;
+            int *orow = reinterpret_cast<int *>(a.out + (static_cast<int64_t>(R) * a.F + col0 + n16));
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if (g == (R & 3) && acc[t][i] != 0) atomicAdd(orow + 16 * t, acc[t][i]);
+        }
+    }
+    if (a.absmax) {
+        float m = static_cast<float>(maxabs) * sc;
+        m = tango_wave_max(m);
+        if (lane == 0 && m > 0.0f) tango_atomic_max_nonneg(a.absmax, m);
+    }
 }

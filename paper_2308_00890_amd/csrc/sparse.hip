@@ -265,6 +265,7 @@ __device__ inline void transpose4x4(uint32_t r0, uint32_t r1, uint32_t r2, uint3
 // the row of dOut_q[v] gathered for 5' is also multiplied with the resident row X_q[u], which is dalpha of edge
 // (u -> v); with alpha (already recomputed for the edge weight), P[v] and the sign of the pre-activation this gives
 // dE, summed into dS_acc[u][h] - the second gather pass over the same rows that a separate SDDMM would need is gone.
+// (k_rev_blocks does the same in blocks of 64 edges where pick_rev_slice says so.)
 // LPHC (DS only): lanes per head when known at compile time (0: computed from the arguments), so that the lane-group
 // sums in the gather loop carry no branches.
 template <int VEC, bool HAS_EID, int WMODE, bool X4 = false, bool DS = false, int LPHC = 0>
@@ -1362,6 +1363,51 @@ int launch_dot_blocks(const sddmm_dot_args &a, int sw, hipStream_t st)
     return TANGO_OK;
 }
 
+// Slice of a row that k_rev_blocks works on: the widest of 128, 64, 32 bytes that divides the row and holds one to four whole
+// heads of at least 16 columns; 0: none, a table beyond its offsets, or the walk that takes whole rows (the DS form of k_spmm) is
+// the faster one.  A row of one slice is always faster in blocks.  With two slices each of them goes through the edge list and
+// fetches the records of its heads again, which short rows pay back and long ones do not; three are about even at mean degree 17 and
+// lose beyond.  Measured over R-MAT graphs, whole rows against blocks in us -
+//   6 M edges at mean degree 17, 100 and 600:  1x32 588:151, 216:101, 147:89   1x128 739:252, 274:155, 188:131   2x64 751:280, 290:178, 201:148
+//   6 M edges at 17, 40 and 100:               2x128 722:486, 434:348, 289:291   4x32 774:408, 463:306, 312:261   4x64 738:539, 456:400, 312:335
+//                                              8x16 974:661, 610:504, 434:443   8x32 1218:786, 790:605, 552:504
+//   40 M edges at 17, 40 and 64:               2x128 3929:2997, 2411:2210, 1936:1944   4x64 4061:3194, 2561:2400, 2080:2141
+//                                              3x128 4643:4531, 3071:3368, 2610:2976
+int pick_rev_slice(int64_t n, int64_t nnz, int heads, int dim)
+{
+    const int F = heads * dim;
+    if (n >= (int64_t(1) << 24) || n * F >= (int64_t(1) << 32) || dim < 16) return 0;
+    for (int sw = 128; sw >= 32; sw /= 2) {
+        if (F % sw != 0 || sw % dim != 0 || sw / dim > 4) continue;
+        const int slices = F / sw;
+        return slices == 1 || (slices == 2 && nnz / n <= 48) ? sw : 0;
+    }
+    return 0;
+}
+
+int launch_rev_blocks(const spmm_args &a, int sw, hipStream_t st)
+{
+    bw_grid gs;
+    const unsigned blocks = bw_grid_for(a.nnz, a.chunk_shift, a.F / sw, gs);
+    const int hs = sw / a.dim;
+#define TANGO_REV(SW_, HS_) k_rev_blocks<SW_, HS_><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a, gs)
+    if (sw == 128) {
+        if (hs == 1) TANGO_REV(128, 1);
+        else if (hs == 2) TANGO_REV(128, 2);
+        else TANGO_REV(128, 4);
+    } else if (sw == 64) {
+        if (hs == 1) TANGO_REV(64, 1);
+        else if (hs == 2) TANGO_REV(64, 2);
+        else TANGO_REV(64, 4);
+    } else {
+        if (hs == 1) TANGO_REV(32, 1);
+        else TANGO_REV(32, 2);
+    }
+#undef TANGO_REV
+    TANGO_LAUNCH_CHECK();
+    return TANGO_OK;
+}
+
 template <int WMODE, bool HAS_EID, bool KEEP = false>
 int launch_spmm_blocks(const spmm_args &a, int sw, hipStream_t st)
 {
@@ -1536,6 +1582,13 @@ static int spmm_launch(const tango_graph *g, int direction, int heads, int dim, 
             return TANGO_OK;
         }
         if (att && att->rec) {  // reverse attention SPMM fused with step 3'
+            if (const int rsw = pick_rev_slice(a.n, a.nnz, heads, dim)) {
+                const int rc = launch_rev_blocks(a, rsw, st);
+                if (rc != TANGO_OK) return rc;
+                k_spmm_finalize<<<row_blocks, 256, 0, st>>>(a);
+                TANGO_LAUNCH_CHECK();
+                return TANGO_OK;
+            }
             switch (pick_vec(a.F, dim, true)) {
                 case 4: k_spmm<4, true, W_ATT_REV, false, true><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a); break;
                 case 8: k_spmm<8, true, W_ATT_REV, false, true><<<blocks, 64 * WAVES_PER_BLOCK, 0, st>>>(a); break;

@@ -126,7 +126,7 @@ def test_fused_attention_forward_backward(T, gname, heads, dim, rounding):
     assert_close(host(dS4), w_dS, "dS (halves)")
 
 
-@pytest.mark.parametrize("heads,dim", [(1, 32), (2, 16), (3, 32), (4, 16), (1, 64), (2, 32), (3, 64), (4, 32), (2, 64), (1, 128), (3, 128), (4, 64), (2, 128)])
+@pytest.mark.parametrize("heads,dim", [(1, 32), (2, 16), (3, 32), (4, 16), (1, 64), (2, 32), (3, 64), (4, 32), (2, 64), (1, 128), (3, 128), (4, 64), (2, 128), (8, 32)])
 def test_fused_attention_block_walk(T, heads, dim):
     """The walks in blocks of 64 edges at every slice width and head count of a slice, on rows that meet every edge of a block."""
     test_fused_attention_forward_backward(T, "blocks", heads, dim, orc.SR)
