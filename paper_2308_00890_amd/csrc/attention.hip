@@ -126,7 +126,7 @@ struct attn_stats_op {
     }
 };
 
-// The workgroups below huge_blocks take the rows longer than HUGE_ROW, a whole workgroup per row; the others walk the
+// The workgroups below huge_blocks take the rows longer than LONG_ROW, a whole workgroup per row; the others walk the
 // remaining rows with a group of lanes per row.  One launch: the hub rows no longer wait for the short ones.
 template <int H, int GROUP>
 __global__ __launch_bounds__(256) void k_attn_stats(int n, const int32_t *ptr, attn_stats_op<H> op, const float *sS,
@@ -138,9 +138,9 @@ __global__ __launch_bounds__(256) void k_attn_stats(int n, const int32_t *ptr, a
     op.sD = *sD;
     op.amax = 0.0f;
     if (static_cast<int>(blockIdx.x) < huge_blocks)
-        walk_huge_rows_strided(ptr, n, static_cast<int>(blockIdx.x), huge_blocks, op, scratch, list);
+        walk_huge_rows_strided(ptr, n, static_cast<int>(blockIdx.x), huge_blocks, op, scratch, list, LONG_ROW);
     else
-        walk_rows<GROUP>(ptr, n, op, nullptr, huge_blocks, huge_blocks > 0, rows_per_wave);
+        walk_rows<GROUP>(ptr, n, op, nullptr, huge_blocks, huge_blocks > 0, rows_per_wave, LONG_ROW);
     tango_block_max_update(op.amax, absmax_alpha);
 }
 
@@ -268,8 +268,8 @@ int tango_attn_stats_async(const tango_graph *g, int heads, const int8_t *Sq, co
         int rc = tango_fill_u32_async(reinterpret_cast<uint32_t *>(absmax_alpha), 0u, 1, st);
         if (rc != TANGO_OK) return rc;
     }
-    // no row can be longer than HUGE_ROW unless the graph has that many edges
-    const int huge_blocks = g->n_edges > HUGE_ROW ? static_cast<int>(std::min<int64_t>(HUGE_GRID, n)) : 0;
+    // no row can be longer than LONG_ROW unless the graph has that many edges
+    const int huge_blocks = g->n_edges > LONG_ROW ? static_cast<int>(std::min<int64_t>(HUGE_GRID, n)) : 0;
 #define CALL(HH)                                                                                             \
     {                                                                                                        \
         attn_stats_op<HH> op{g->in_src, Sq, Dq, 0.f, 0.f, slope, row_lse, 0.f, src_codes};                   \

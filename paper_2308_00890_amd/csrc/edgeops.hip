@@ -3,15 +3,67 @@
 // edge-to-node sums (steps 3', 3''; Sec. 3.3 Fig. 5), edge softmax forward and
 // backward (steps 4, 4'; Sec. 3.2 keeps them in fp32).
 //
-// All of them stream the destination-major edge arrays once or a few times
-// and are bound by HBM bandwidth.  Rows (nodes) are handed out in blocks of 64
-// consecutive rows per wavefront; short rows are processed by groups of GROUP
-// lanes (GROUP ~ the mean degree), rows longer than 16*GROUP by the whole
-// wave, one lane per edge with all heads of that edge.
+// All of them stream the destination-major edge arrays once or a few times; what bounds them is the chain of
+// dependent loads of a row (codes of the other end through its index) rather than bandwidth.  Rows (nodes) are handed
+// out in blocks of consecutive rows per wavefront; short rows are processed by groups of GROUP lanes (GROUP ~ the
+// mean degree), rows longer than 16*GROUP by the whole wave and rows longer than LONG_ROW by a whole workgroup of the same
+// launch, one lane per edge with all heads of that edge, four edges per lane in flight.  Without the last two a hub row
+// of some thousand edges is one wave's chain of some hundred round trips: 50 K nodes, 2 M edges of a power-law graph,
+// two heads: softmax 131 -> 39 us, its backward 91 -> 26, add 76 -> 26, its backward 96 -> 26 (dD) and 124 -> 52 (dS).
+#include <algorithm>
+#include <type_traits>
+
 #include "internal.hip.h"
+#include "attn_math.hip.h"
 #include "rowwalk.hip.h"
 
 namespace {
+
+struct row_split {
+    int long_blocks;    // workgroups below this one take the long rows
+    int rows_per_wave;  // see walk_rows
+    unsigned grid;
+};
+
+row_split split_rows(int n, int64_t nnz, int group)
+{
+    row_split r;
+    r.rows_per_wave = pick_rows_per_wave(n, group);
+    r.long_blocks = nnz > LONG_ROW ? static_cast<int>(std::min<int64_t>(HUGE_GRID, n)) : 0;  // (no row can be longer otherwise)
+    r.grid = row_grid(n, group, r.rows_per_wave) + r.long_blocks;
+    return r;
+}
+
+template <int GROUP, class Op>
+__device__ inline void walk_all_rows(const int32_t *ptr, int n, Op &op, int long_blocks, int rows_per_wave)
+{
+    __shared__ double scratch[2 * 256 / 64];
+    __shared__ int list[256 + 1];
+    if (static_cast<int>(blockIdx.x) < long_blocks)
+        walk_huge_rows_strided(ptr, n, static_cast<int>(blockIdx.x), long_blocks, op, scratch, list, LONG_ROW);
+    else
+        walk_rows<GROUP>(ptr, n, op, nullptr, long_blocks, long_blocks > 0, rows_per_wave, LONG_ROW);
+}
+
+// The codes of a node; whole: the table is aligned to H bytes (H 2, 4 or 8), one load.
+template <int H>
+__device__ inline void load_codes(const int8_t *table, int64_t node, bool whole, int (&v)[H])
+{
+    if (whole) {
+        tango_load_heads<H>(table, node, v);
+    } else {
+#pragma unroll
+        for (int h = 0; h < H; ++h) v[h] = static_cast<int>(table[node * H + h]);
+    }
+}
+
+// body(e0, k): the edges e0, e0 + step, ... (k of them, 4 or 1, k a compile-time constant) of the range [e, t)
+template <class Body>
+__device__ inline void by_four(int e, int t, int step, Body body)
+{
+    for (; t - e > 3 * step; e += 4 * step) body(e, std::integral_constant<int, 4>{});
+    for (; e < t; e += step) body(e, std::integral_constant<int, 1>{});
+}
 
 // ------------------------------------------------------------------ SDDMM-add
 template <int H>
@@ -20,33 +72,43 @@ struct sddmm_add_op {
     const int8_t *Sq, *Dq;
     float sS, sD, slope;
     float *E;
+    bool whole;
     template <class Team>
     __device__ void run(int row, int b, int t, Team tm)
     {
         float td[H];
 #pragma unroll
         for (int h = 0; h < H; ++h) td[h] = sD * static_cast<float>(Dq[static_cast<int64_t>(row) * H + h]);
-        for (int e = b + tm.rank; e < t; e += tm.size()) {
-            const int64_t u = src[e];
-            float v[H];
+        by_four(b + tm.rank, t, tm.size(), [&](int e, auto K) __attribute__((always_inline)) {
+            constexpr int N = decltype(K)::value;
+            int sq[N][H];
+            int u[N];
 #pragma unroll
-            for (int h = 0; h < H; ++h) {
-                const float ts = sS * static_cast<float>(Sq[u * H + h]);
-                const float x = ts + td[h];
-                v[h] = x > 0.0f ? x : slope * x;
+            for (int i = 0; i < N; ++i) u[i] = src[e + i * tm.size()];
+#pragma unroll
+            for (int i = 0; i < N; ++i) load_codes<H>(Sq, u[i], whole, sq[i]);
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                float v[H];
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    const float ts = sS * static_cast<float>(sq[i][h]);
+                    const float x = ts + td[h];
+                    v[h] = x > 0.0f ? x : slope * x;
+                }
+                store_h<H>(E + static_cast<int64_t>(e + i * tm.size()) * H, v);
             }
-            store_h<H>(E + static_cast<int64_t>(e) * H, v);
-        }
+        });
     }
 };
 
 template <int H, int GROUP>
 __global__ __launch_bounds__(256) void k_sddmm_add(int n, const int32_t *ptr, sddmm_add_op<H> op, const float *sS,
-                                                   const float *sD)
+                                                   const float *sD, int long_blocks, int rows_per_wave)
 {
     op.sS = *sS;
     op.sD = *sD;
-    walk_rows<GROUP>(ptr, n, op);
+    walk_all_rows<GROUP>(ptr, n, op, long_blocks, rows_per_wave);
 }
 
 // dD[v][h] = sum over in-edges of dE*lrelu'(t); optional dE_pre.
@@ -57,6 +119,7 @@ struct sddmm_add_bwd_dst_op {
     float sS, sD, slope;
     const float *dE;
     float *dEpre, *dD;
+    bool whole;
     template <class Team>
     __device__ void run(int row, int b, int t, Team tm)
     {
@@ -67,19 +130,29 @@ struct sddmm_add_bwd_dst_op {
             td[h] = sD * static_cast<float>(Dq[static_cast<int64_t>(row) * H + h]);
             acc[h] = 0.0;
         }
-        for (int e = b + tm.rank; e < t; e += tm.size()) {
-            const int64_t u = src[e];
-            float g[H];
-            load_h<H>(dE + static_cast<int64_t>(e) * H, g);
+        by_four(b + tm.rank, t, tm.size(), [&](int e, auto K) __attribute__((always_inline)) {
+            constexpr int N = decltype(K)::value;
+            int sq[N][H];
+            int u[N];
+            float g[N][H];
 #pragma unroll
-            for (int h = 0; h < H; ++h) {
-                const float ts = sS * static_cast<float>(Sq[u * H + h]);
-                const float x = ts + td[h];
-                g[h] = g[h] * (x > 0.0f ? 1.0f : slope);
-                acc[h] += static_cast<double>(g[h]);
+            for (int i = 0; i < N; ++i) u[i] = src[e + i * tm.size()];
+#pragma unroll
+            for (int i = 0; i < N; ++i) load_h<H>(dE + static_cast<int64_t>(e + i * tm.size()) * H, g[i]);
+#pragma unroll
+            for (int i = 0; i < N; ++i) load_codes<H>(Sq, u[i], whole, sq[i]);
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    const float ts = sS * static_cast<float>(sq[i][h]);
+                    const float x = ts + td[h];
+                    g[i][h] = g[i][h] * (x > 0.0f ? 1.0f : slope);
+                    acc[h] += static_cast<double>(g[i][h]);
+                }
+                if (dEpre) store_h<H>(dEpre + static_cast<int64_t>(e + i * tm.size()) * H, g[i]);
             }
-            if (dEpre) store_h<H>(dEpre + static_cast<int64_t>(e) * H, g);
-        }
+        });
 #pragma unroll
         for (int h = 0; h < H; ++h) {
             const double s = tm.sum(acc[h]);
@@ -90,11 +163,11 @@ struct sddmm_add_bwd_dst_op {
 
 template <int H, int GROUP>
 __global__ __launch_bounds__(256) void k_sddmm_add_bwd_dst(int n, const int32_t *ptr, sddmm_add_bwd_dst_op<H> op,
-                                                           const float *sS, const float *sD)
+                                                           const float *sS, const float *sD, int long_blocks, int rows_per_wave)
 {
     op.sS = *sS;
     op.sD = *sD;
-    walk_rows<GROUP>(ptr, n, op);
+    walk_all_rows<GROUP>(ptr, n, op, long_blocks, rows_per_wave);
 }
 
 // dS[u][h] = sum over out-edges of dE[eid]*lrelu'(t), t recomputed from S_q[u], D_q[dst].
@@ -105,6 +178,7 @@ struct sddmm_add_bwd_src_op {
     float sS, sD, slope;
     const float *dE;
     float *dS;
+    bool whole;
     template <class Team>
     __device__ void run(int row, int b, int t, Team tm)
     {
@@ -115,18 +189,30 @@ struct sddmm_add_bwd_src_op {
             ts[h] = sS * static_cast<float>(Sq[static_cast<int64_t>(row) * H + h]);
             acc[h] = 0.0;
         }
-        for (int j = b + tm.rank; j < t; j += tm.size()) {
-            const int64_t v = dst[j];
-            const int64_t e = eid[j];
-            float g[H];
-            load_h<H>(dE + e * H, g);
+        by_four(b + tm.rank, t, tm.size(), [&](int j, auto K) __attribute__((always_inline)) {
+            constexpr int N = decltype(K)::value;
+            int dq[N][H];
+            int v[N], e[N];
+            float g[N][H];
 #pragma unroll
-            for (int h = 0; h < H; ++h) {
-                const float tdv = sD * static_cast<float>(Dq[v * H + h]);
-                const float x = ts[h] + tdv;
-                acc[h] += static_cast<double>(g[h] * (x > 0.0f ? 1.0f : slope));
+            for (int i = 0; i < N; ++i) {
+                v[i] = dst[j + i * tm.size()];
+                e[i] = eid[j + i * tm.size()];
             }
-        }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                load_h<H>(dE + static_cast<int64_t>(e[i]) * H, g[i]);
+                load_codes<H>(Dq, v[i], whole, dq[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    const float tdv = sD * static_cast<float>(dq[i][h]);
+                    const float x = ts[h] + tdv;
+                    acc[h] += static_cast<double>(g[i][h] * (x > 0.0f ? 1.0f : slope));
+                }
+        });
 #pragma unroll
         for (int h = 0; h < H; ++h) {
             const double s = tm.sum(acc[h]);
@@ -137,11 +223,11 @@ struct sddmm_add_bwd_src_op {
 
 template <int H, int GROUP>
 __global__ __launch_bounds__(256) void k_sddmm_add_bwd_src(int n, const int32_t *ptr, sddmm_add_bwd_src_op<H> op,
-                                                           const float *sS, const float *sD)
+                                                           const float *sS, const float *sD, int long_blocks, int rows_per_wave)
 {
     op.sS = *sS;
     op.sD = *sD;
-    walk_rows<GROUP>(ptr, n, op);
+    walk_all_rows<GROUP>(ptr, n, op, long_blocks, rows_per_wave);
 }
 
 // ------------------------------------------------------------------ edge softmax
@@ -159,40 +245,94 @@ struct softmax_op {
             m[h] = -INFINITY;
             s[h] = 0.0f;
         }
-        for (int e = b + tm.rank; e < t; e += tm.size()) {
-            float v[H];
-            load_h<H>(E + static_cast<int64_t>(e) * H, v);
+        constexpr int UE = H >= 8 ? 2 : 4;
+        if (t - b <= UE * tm.size()) {  // the row fits the team's registers: one pass over memory
+            float v[UE][H];
 #pragma unroll
-            for (int h = 0; h < H; ++h) m[h] = fmaxf(m[h], v[h]);
-        }
+            for (int i = 0; i < UE; ++i) {
 #pragma unroll
-        for (int h = 0; h < H; ++h) m[h] = tm.max(m[h]);
-        for (int e = b + tm.rank; e < t; e += tm.size()) {
-            float v[H];
-            load_h<H>(E + static_cast<int64_t>(e) * H, v);
-#pragma unroll
-            for (int h = 0; h < H; ++h) s[h] += expf(v[h] - m[h]);
-        }
-#pragma unroll
-        for (int h = 0; h < H; ++h) s[h] = tm.sum(s[h]);
-        for (int e = b + tm.rank; e < t; e += tm.size()) {
-            float v[H];
-            load_h<H>(E + static_cast<int64_t>(e) * H, v);
+                for (int h = 0; h < H; ++h) v[i][h] = -INFINITY;
+                const int e = b + tm.rank + i * tm.size();
+                if (e < t) load_h<H>(E + static_cast<int64_t>(e) * H, v[i]);
+            }
 #pragma unroll
             for (int h = 0; h < H; ++h) {
-                v[h] = expf(v[h] - m[h]) / s[h];
-                amax = fmaxf(amax, v[h]);
+#pragma unroll
+                for (int i = 0; i < UE; ++i) m[h] = fmaxf(m[h], v[i][h]);
+                m[h] = tm.max(m[h]);
             }
-            store_h<H>(alpha + static_cast<int64_t>(e) * H, v);
+#pragma unroll
+            for (int i = 0; i < UE; ++i)
+                if (b + tm.rank + i * tm.size() < t) {
+#pragma unroll
+                    for (int h = 0; h < H; ++h) {
+                        v[i][h] = expf(v[i][h] - m[h]);
+                        s[h] += v[i][h];
+                    }
+                }
+#pragma unroll
+            for (int h = 0; h < H; ++h) s[h] = tm.sum(s[h]);
+#pragma unroll
+            for (int i = 0; i < UE; ++i) {
+                const int e = b + tm.rank + i * tm.size();
+                if (e >= t) continue;
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    v[i][h] = v[i][h] / s[h];
+                    amax = fmaxf(amax, v[i][h]);
+                }
+                store_h<H>(alpha + static_cast<int64_t>(e) * H, v[i]);
+            }
+            return;
         }
+        by_four(b + tm.rank, t, tm.size(), [&](int e, auto K) __attribute__((always_inline)) {
+            constexpr int N = decltype(K)::value;
+            float v[N][H];
+#pragma unroll
+            for (int i = 0; i < N; ++i) load_h<H>(E + static_cast<int64_t>(e + i * tm.size()) * H, v[i]);
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+#pragma unroll
+                for (int h = 0; h < H; ++h) m[h] = fmaxf(m[h], v[i][h]);
+        });
+#pragma unroll
+        for (int h = 0; h < H; ++h) m[h] = tm.max(m[h]);
+        by_four(b + tm.rank, t, tm.size(), [&](int e, auto K) __attribute__((always_inline)) {
+            constexpr int N = decltype(K)::value;
+            float v[N][H];
+#pragma unroll
+            for (int i = 0; i < N; ++i) load_h<H>(E + static_cast<int64_t>(e + i * tm.size()) * H, v[i]);
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+#pragma unroll
+                for (int h = 0; h < H; ++h) s[h] += expf(v[i][h] - m[h]);
+        });
+#pragma unroll
+        for (int h = 0; h < H; ++h) s[h] = tm.sum(s[h]);
+        by_four(b + tm.rank, t, tm.size(), [&](int e, auto K) __attribute__((always_inline)) {
+            constexpr int N = decltype(K)::value;
+            float v[N][H];
+#pragma unroll
+            for (int i = 0; i < N; ++i) load_h<H>(E + static_cast<int64_t>(e + i * tm.size()) * H, v[i]);
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    v[i][h] = expf(v[i][h] - m[h]) / s[h];
+                    amax = fmaxf(amax, v[i][h]);
+                }
+                store_h<H>(alpha + static_cast<int64_t>(e + i * tm.size()) * H, v[i]);
+            }
+        });
     }
 };
 
 template <int H, int GROUP>
-__global__ __launch_bounds__(256) void k_edge_softmax(int n, const int32_t *ptr, softmax_op<H> op, float *absmax)
+__global__ __launch_bounds__(256) void k_edge_softmax(int n, const int32_t *ptr, softmax_op<H> op, float *absmax, int long_blocks,
+                                                      int rows_per_wave)
 {
     op.amax = 0.0f;
-    walk_rows<GROUP>(ptr, n, op);
+    walk_all_rows<GROUP>(ptr, n, op, long_blocks, rows_per_wave);
     if (absmax) tango_block_max_update(op.amax, absmax);
 }
 
@@ -206,31 +346,76 @@ struct softmax_bwd_op {
         double P[H];
 #pragma unroll
         for (int h = 0; h < H; ++h) P[h] = 0.0;
-        for (int e = b + tm.rank; e < t; e += tm.size()) {
-            float a[H], d[H];
-            load_h<H>(alpha + static_cast<int64_t>(e) * H, a);
-            load_h<H>(dalpha + static_cast<int64_t>(e) * H, d);
+        constexpr int UE = H >= 8 ? 1 : 4;
+        if (t - b <= UE * tm.size()) {  // the row fits the team's registers
+            float a[UE][H], d[UE][H];
 #pragma unroll
-            for (int h = 0; h < H; ++h) P[h] += static_cast<double>(d[h]) * static_cast<double>(a[h]);
+            for (int i = 0; i < UE; ++i) {
+                const int e = b + tm.rank + i * tm.size();
+#pragma unroll
+                for (int h = 0; h < H; ++h) a[i][h] = d[i][h] = 0.0f;
+                if (e < t) {
+                    load_h<H>(alpha + static_cast<int64_t>(e) * H, a[i]);
+                    load_h<H>(dalpha + static_cast<int64_t>(e) * H, d[i]);
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+#pragma unroll
+                for (int i = 0; i < UE; ++i) P[h] += static_cast<double>(d[i][h]) * static_cast<double>(a[i][h]);
+                P[h] = tm.sum(P[h]);
+            }
+#pragma unroll
+            for (int i = 0; i < UE; ++i) {
+                const int e = b + tm.rank + i * tm.size();
+                if (e >= t) continue;
+                float o[H];
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+                    o[h] = static_cast<float>(static_cast<double>(a[i][h]) * (static_cast<double>(d[i][h]) - P[h]));
+                store_h<H>(dE + static_cast<int64_t>(e) * H, o);
+            }
+            return;
         }
+        by_four(b + tm.rank, t, tm.size(), [&](int e, auto K) __attribute__((always_inline)) {
+            constexpr int N = decltype(K)::value;
+            float a[N][H], d[N][H];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                load_h<H>(alpha + static_cast<int64_t>(e + i * tm.size()) * H, a[i]);
+                load_h<H>(dalpha + static_cast<int64_t>(e + i * tm.size()) * H, d[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+#pragma unroll
+                for (int h = 0; h < H; ++h) P[h] += static_cast<double>(d[i][h]) * static_cast<double>(a[i][h]);
+        });
 #pragma unroll
         for (int h = 0; h < H; ++h) P[h] = tm.sum(P[h]);
-        for (int e = b + tm.rank; e < t; e += tm.size()) {
-            float a[H], d[H], o[H];
-            load_h<H>(alpha + static_cast<int64_t>(e) * H, a);
-            load_h<H>(dalpha + static_cast<int64_t>(e) * H, d);
+        by_four(b + tm.rank, t, tm.size(), [&](int e, auto K) __attribute__((always_inline)) {
+            constexpr int N = decltype(K)::value;
+            float a[N][H], d[N][H];
 #pragma unroll
-            for (int h = 0; h < H; ++h)
-                o[h] = static_cast<float>(static_cast<double>(a[h]) * (static_cast<double>(d[h]) - P[h]));
-            store_h<H>(dE + static_cast<int64_t>(e) * H, o);
-        }
+            for (int i = 0; i < N; ++i) {
+                load_h<H>(alpha + static_cast<int64_t>(e + i * tm.size()) * H, a[i]);
+                load_h<H>(dalpha + static_cast<int64_t>(e + i * tm.size()) * H, d[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                float o[H];
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+                    o[h] = static_cast<float>(static_cast<double>(a[i][h]) * (static_cast<double>(d[i][h]) - P[h]));
+                store_h<H>(dE + static_cast<int64_t>(e + i * tm.size()) * H, o);
+            }
+        });
     }
 };
 
 template <int H, int GROUP>
-__global__ __launch_bounds__(256) void k_edge_softmax_bwd(int n, const int32_t *ptr, softmax_bwd_op<H> op)
+__global__ __launch_bounds__(256) void k_edge_softmax_bwd(int n, const int32_t *ptr, softmax_bwd_op<H> op, int long_blocks, int rows_per_wave)
 {
-    walk_rows<GROUP>(ptr, n, op);
+    walk_all_rows<GROUP>(ptr, n, op, long_blocks, rows_per_wave);
 }
 
 }  // namespace
@@ -240,11 +425,11 @@ int tango_sddmm_add_async(const tango_graph *g, int heads, const int8_t *Sq, con
 {
     const int n = g->n_nodes;
     const int grp = pick_group(n, g->n_edges);
-    const unsigned grid = row_grid(n, grp);
-#define CALL(HH)                                                                        \
-    {                                                                                   \
-        sddmm_add_op<HH> op{g->in_src, Sq, Dq, 0.f, 0.f, slope, E};                     \
-        k_sddmm_add<HH, GROUP><<<grid, 256, 0, st>>>(n, g->in_ptr, op, sS, sD);         \
+    const row_split sp = split_rows(n, g->n_edges, grp);
+#define CALL(HH) \
+    { \
+        sddmm_add_op<HH> op{g->in_src, Sq, Dq, 0.f, 0.f, slope, E, tango_aligned(Sq, HH)}; \
+        k_sddmm_add<HH, GROUP><<<sp.grid, 256, 0, st>>>(n, g->in_ptr, op, sS, sD, sp.long_blocks, sp.rows_per_wave); \
     }
     TANGO_DISPATCH_H(heads, grp, CALL)
 #undef CALL
@@ -258,22 +443,22 @@ int tango_sddmm_add_bwd_async(const tango_graph *g, int heads, const int8_t *Sq,
 {
     const int n = g->n_nodes;
     const int grp = pick_group(n, g->n_edges);
-    const unsigned grid = row_grid(n, grp);
+    const row_split sp = split_rows(n, g->n_edges, grp);
     if (dD || dEpre) {
-#define CALL(HH)                                                                                \
-    {                                                                                           \
-        sddmm_add_bwd_dst_op<HH> op{g->in_src, Sq, Dq, 0.f, 0.f, slope, dE, dEpre, dD};         \
-        k_sddmm_add_bwd_dst<HH, GROUP><<<grid, 256, 0, st>>>(n, g->in_ptr, op, sS, sD);         \
+#define CALL(HH) \
+    { \
+        sddmm_add_bwd_dst_op<HH> op{g->in_src, Sq, Dq, 0.f, 0.f, slope, dE, dEpre, dD, tango_aligned(Sq, HH)}; \
+        k_sddmm_add_bwd_dst<HH, GROUP><<<sp.grid, 256, 0, st>>>(n, g->in_ptr, op, sS, sD, sp.long_blocks, sp.rows_per_wave); \
     }
         TANGO_DISPATCH_H(heads, grp, CALL)
 #undef CALL
         TANGO_LAUNCH_CHECK();
     }
     if (dS) {
-#define CALL(HH)                                                                                \
-    {                                                                                           \
-        sddmm_add_bwd_src_op<HH> op{g->out_dst, g->out_eid, Sq, Dq, 0.f, 0.f, slope, dE, dS};   \
-        k_sddmm_add_bwd_src<HH, GROUP><<<grid, 256, 0, st>>>(n, g->out_ptr, op, sS, sD);        \
+#define CALL(HH) \
+    { \
+        sddmm_add_bwd_src_op<HH> op{g->out_dst, g->out_eid, Sq, Dq, 0.f, 0.f, slope, dE, dS, tango_aligned(Dq, HH)}; \
+        k_sddmm_add_bwd_src<HH, GROUP><<<sp.grid, 256, 0, st>>>(n, g->out_ptr, op, sS, sD, sp.long_blocks, sp.rows_per_wave); \
     }
         TANGO_DISPATCH_H(heads, grp, CALL)
 #undef CALL
@@ -287,15 +472,15 @@ int tango_edge_softmax_async(const tango_graph *g, int heads, const float *E, fl
 {
     const int n = g->n_nodes;
     const int grp = pick_group(n, g->n_edges);
-    const unsigned grid = row_grid(n, grp);
+    const row_split sp = split_rows(n, g->n_edges, grp);
     if (absmax) {
         int rc = tango_fill_u32_async(reinterpret_cast<uint32_t *>(absmax), 0u, 1, st);
         if (rc != TANGO_OK) return rc;
     }
-#define CALL(HH)                                                                    \
-    {                                                                               \
-        softmax_op<HH> op{E, alpha, 0.f};                                           \
-        k_edge_softmax<HH, GROUP><<<grid, 256, 0, st>>>(n, g->in_ptr, op, absmax);  \
+#define CALL(HH) \
+    { \
+        softmax_op<HH> op{E, alpha, 0.f}; \
+        k_edge_softmax<HH, GROUP><<<sp.grid, 256, 0, st>>>(n, g->in_ptr, op, absmax, sp.long_blocks, sp.rows_per_wave); \
     }
     TANGO_DISPATCH_H(heads, grp, CALL)
 #undef CALL
@@ -308,11 +493,11 @@ int tango_edge_softmax_bwd_async(const tango_graph *g, int heads, const float *a
 {
     const int n = g->n_nodes;
     const int grp = pick_group(n, g->n_edges);
-    const unsigned grid = row_grid(n, grp);
-#define CALL(HH)                                                                \
-    {                                                                           \
-        softmax_bwd_op<HH> op{alpha, dalpha, dE};                               \
-        k_edge_softmax_bwd<HH, GROUP><<<grid, 256, 0, st>>>(n, g->in_ptr, op);  \
+    const row_split sp = split_rows(n, g->n_edges, grp);
+#define CALL(HH) \
+    { \
+        softmax_bwd_op<HH> op{alpha, dalpha, dE}; \
+        k_edge_softmax_bwd<HH, GROUP><<<sp.grid, 256, 0, st>>>(n, g->in_ptr, op, sp.long_blocks, sp.rows_per_wave); \
     }
     TANGO_DISPATCH_H(heads, grp, CALL)
 #undef CALL

@@ -141,12 +141,12 @@ inline size_t huge_list_bytes(int64_t nnz) { return tango_round_up(static_cast<s
 // huge: NULL, or a list (huge[0] = count, zero-initialised; huge[1..] = rows) that receives rows longer than
 // HUGE_ROW instead of processing them here.
 // first_block, skip_huge: the launch's workgroups below first_block do something else (walk_huge_rows_strided) and the
-// rows longer than HUGE_ROW are theirs: skipped here, no list.
+// rows longer than huge_row are theirs: skipped here, no list.
 // rows_per_wave (groups of fewer than 64 lanes only; a power of two, 64 / GROUP <= rows_per_wave <= 64): the rows a wave
 // takes per outer iteration - fewer on small graphs, so that more waves share them.
 template <int GROUP, class Op>
 __device__ inline void walk_rows(const int32_t *__restrict__ ptr, int n, Op &op, int *huge = nullptr, int first_block = 0,
-                                 bool skip_huge = false, int rows_per_wave = 64)
+                                 bool skip_huge = false, int rows_per_wave = 64, int huge_row = HUGE_ROW)
 {
     const int lane = threadIdx.x % TANGO_WAVE;
     // readfirstlane / readlane: the wave index and the bounds of a row taken by the whole wave are wave-uniform, and
@@ -166,7 +166,7 @@ __device__ inline void walk_rows(const int32_t *__restrict__ ptr, int n, Op &op,
             t = ptr[r + 1];
         }
         int is_long = (GROUP == 64) ? 1 : ((t - b) > 16 * GROUP ? 1 : 0);
-        if ((huge || skip_huge) && r < n && (t - b) > HUGE_ROW) {
+        if ((huge || skip_huge) && r < n && (t - b) > huge_row) {
             if (huge) huge[1 + atomicAdd(huge, 1)] = r;
             is_long = 2;  // neither a group nor this wave processes it
         }
@@ -201,16 +201,16 @@ __device__ inline void walk_huge_rows(const int32_t *__restrict__ ptr, const int
 
 // The same without a list, inside the launch that walks the other rows: workgroup j of nblocks looks at the rows
 // j, j + nblocks, ... (strided, so that hubs clustered at neighbouring ids spread over the workgroups), collects those
-// longer than HUGE_ROW, up to one per thread and round, in LDS (list: blockDim.x + 1 ints) and takes them one by one.
+// longer than huge_row, up to one per thread and round, in LDS (list: blockDim.x + 1 ints) and takes them one by one.
 template <class Op>
 __device__ inline void walk_huge_rows_strided(const int32_t *__restrict__ ptr, int n, int j, int nblocks, Op &op,
-                                              double *scratch, int *list)
+                                              double *scratch, int *list, int huge_row = HUGE_ROW)
 {
     for (int64_t r0 = j; r0 < n; r0 += static_cast<int64_t>(nblocks) * blockDim.x) {
         if (threadIdx.x == 0) list[0] = 0;
         __syncthreads();
         const int64_t r = r0 + static_cast<int64_t>(threadIdx.x) * nblocks;
-        if (r < n && ptr[r + 1] - ptr[r] > HUGE_ROW) list[1 + atomicAdd(&list[0], 1)] = static_cast<int>(r);
+        if (r < n && ptr[r + 1] - ptr[r] > huge_row) list[1 + atomicAdd(&list[0], 1)] = static_cast<int>(r);
         __syncthreads();
         const int count = list[0];
         for (int i = 0; i < count; ++i) {
@@ -222,6 +222,10 @@ __device__ inline void walk_huge_rows_strided(const int32_t *__restrict__ ptr, i
 }
 
 constexpr unsigned HUGE_GRID = 2048;
+// Where the walk of the long rows is part of the launch, a row of more edges than this is taken by a workgroup of 256
+// threads: four edges for each of them.  (With the limit at HUGE_ROW a wave
+// went through up to 4,096 edges alone: statistics of 1.2 M edges of a citation graph, four heads, 65 -> 60 us.)
+constexpr int LONG_ROW = 1024;
 
 // Rows per wave for walk_rows with groups of `group` lanes: 64, or fewer (down to one per group) while the graph has
 // fewer than 2,048 waves' worth of rows.

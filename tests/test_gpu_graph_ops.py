@@ -281,6 +281,53 @@ def test_edge_softmax_forward_backward(T, gname, heads):
     assert_close(host(dE), orc.edge_softmax_bwd(g, want, dalpha), "dE")
 
 
+@pytest.mark.parametrize("heads", [1, 2, 3, 4, 8])
+@pytest.mark.parametrize("mean", [4, 12, 30, 200])  # one for each number of lanes per row
+def test_edge_primitives_row_lengths(T, heads, mean):
+    """Rows on both sides of every limit of the row walk: what a team of 8 to 64 lanes or a workgroup of 256 threads holds in
+    registers, sixteen edges per lane, the rows that a workgroup takes; and code tables at odd addresses."""
+    import torch
+
+    rng = np.random.default_rng(mean)
+    lengths = [0, 1, 7, 8, 9, 31, 32, 33, 64, 65, 127, 128, 129, 255, 256, 257, 512, 513, 1023, 1024, 1025, 1280, 1500]
+    n = max(1600, (2 * sum(lengths)) // mean)
+    deg = rng.integers(0, max(2 * mean - 2 * sum(lengths) // n, 1) + 1, n)
+    deg[rng.choice(n, len(lengths), replace=False)] = lengths
+    there = np.concatenate([rng.choice(n, d, replace=False) for d in deg if d])
+    here = np.repeat(np.arange(n), deg)
+    dE0 = ti.normal((here.size, heads), 31)
+    codes = [rand_i8((n, heads), 32 + i) for i in range(2)]
+    room = torch.zeros(n * heads + 1, dtype=torch.int8, device="cuda")
+    sS, sD = np.float32(0.031), np.float32(0.027)
+    for src, dst in ((there, here), (here, there)):  # the long rows as destinations, then as sources
+        g = ti.graph_from_edges(n, src, dst, self_loops=False)
+        G = T.Graph.from_host(g)
+        for odd in (False, True):
+            Sq, Dq = dev(codes[0]), dev(codes[1])
+            if odd:
+                room2 = room.clone()
+                for buf, i in ((room, 0), (room2, 1)):
+                    buf[1:] = dev(codes[i]).reshape(-1)
+                Sq, Dq = room[1:].view(n, heads), room2[1:].view(n, heads)
+            E = empty((g.n_edges, heads), torch.float32)
+            T.tango_qsddmm(G, T.SDDMM_ADD_LEAKYRELU, heads, 1, Sq, scalar(sS), Dq, scalar(sD), 0.2, E)
+            assert_bit_exact(host(E), orc.sddmm_add(g, codes[0], sS, codes[1], sD, 0.2), "E")
+            dP, dS, dD = empty((g.n_edges, heads), torch.float32), empty((n, heads), torch.float32), empty((n, heads), torch.float32)
+            T.tango_qsddmm_bwd(G, heads, Sq, scalar(sS), Dq, scalar(sD), 0.2, dev(dE0), dP, dS, dD)
+            w_dE, w_dS, w_dD = orc.sddmm_add_bwd(g, codes[0], sS, codes[1], sD, 0.2, dE0)
+            assert_bit_exact(host(dP), w_dE, "dE_pre")
+            assert_close(host(dS), w_dS, "dS")
+            assert_close(host(dD), w_dD, "dD")
+        alpha, dE, am = empty((g.n_edges, heads), torch.float32), empty((g.n_edges, heads), torch.float32), scalar(-1)
+        score = (3.0 * ti.normal((g.n_edges, heads), 33)).astype(np.float32)
+        T.tango_edge_softmax(G, heads, dev(score), alpha, am)
+        want = orc.edge_softmax(g, score)
+        assert_close(host(alpha), want, "alpha")
+        assert host(am)[0] == host(alpha).max()
+        T.tango_edge_softmax_bwd(G, heads, dev(want), dev(dE0), dE)
+        assert_close(host(dE), orc.edge_softmax_bwd(g, want, dE0), "dE")
+
+
 def test_unsupported_shapes_are_refused(T):
     import torch
 
