@@ -12,11 +12,14 @@
 // result does not depend on the order) and dequantized by a small second
 // kernel.
 //
-// Inside a wave, a feature row of F int8 is covered by LPR = F/VEC lanes that
-// load VEC bytes each, so one wave-wide load instruction gathers G = 64/LPR
+// Inside a wave there are two forms.  In blocks (blockwalk.hip.h: k_spmm_blocks,
+// k_dot_blocks, k_rev_blocks) 64 rows, or column slices of rows, are gathered
+// straight into LDS and multiplied on the matrix cores; the pick_*_slice rules
+// below say where.  Elsewhere (narrow heads, 4-bit tables, long rows of several
+// heads) a feature row of F int8 is covered by LPR = F/VEC lanes that load VEC bytes each, so one wave-wide load instruction gathers G = 64/LPR
 // neighbour rows; the G partial sums are combined with cross-lane shuffles.
 //
-// Roofline: both kernels gather F bytes per edge from the int8 node table;
+// Roofline: all of them gather F bytes per edge from the int8 node table;
 // HBM-bound when the table exceeds the on-chip caches, else bound by the
 // cache/fabric gather rate.  Algorithmic bytes per edge: 4 (index) + heads
 // (weight) + F (row); per node: 4 (pointer) + 4F (fp32 result).
@@ -1320,7 +1323,8 @@ unsigned bw_grid_for(int64_t nnz, int shift, int slices, bw_grid &gs)
 // (k_sddmm_dot) is the faster one.  That walk reads a row's neighbours without a matrix operand to build, so it gains with the
 // row length and with every further head, which costs the block walk an epilogue per (edge, head).  Measured over R-MAT
 // graphs of 6 M edges, lane groups against blocks in us, at mean degree 17, 40 and 100 -
-//   storing:          1x64 163:63, 97:52, 61:43    2x128 220:178, 140:132, 101:114   4x64 237:226, 141:151, 103:131
+//   storing (a row of three slices: 64 M edges at mean degree 26, 3x128, 3.07:3.34 ms, so at most two):
+//                     1x64 163:63, 97:52, 61:43    2x128 220:178, 140:132, 101:114   4x64 237:226, 141:151, 103:131
 //   attention sums:   1x64 377:126, 231:100, 149:80   2x64 422:208, 257:165, 166:138   3x128 587:431, 345:301, 240:252
 //                     4x32 399:326, 255:252, 165:206   4x64 444:428, 260:313, 165:258   8x32 521:667
 int pick_dot_slice(int64_t n, int64_t nnz, int heads, int dim, bool attention)
@@ -1335,7 +1339,7 @@ int pick_dot_slice(int64_t n, int64_t nnz, int heads, int dim, bool attention)
         return 0;
     }
     for (int sw = 128; sw >= 32; sw /= 2)
-        if (F % sw == 0 && sw % dim == 0 && dim >= 16 && sw / dim <= 4) return sw;
+        if (F % sw == 0 && sw % dim == 0 && dim >= 16 && sw / dim <= 4) return !attention && F >= 3 * sw ? 0 : sw;
     return 0;
 }
 
@@ -1525,6 +1529,10 @@ static int spmm_launch(const tango_graph *g, int direction, int heads, int dim, 
     // graphs of 6 M edges, lane groups against blocks in us: 4 x 64 at mean degree 100 147:129, at 250 114:118, at 600 103:110;
     // through the edge-id map 3 x 128 at 40 376:367, at 100 273:287, at 250 234:263.
     if (!att && a.F > sw && static_cast<int64_t>(a.n) * a.F <= (int64_t(16) << 20) && a.nnz / a.n >= (a.eid ? 64 : 200)) sw = 0;
+    // Codes behind the edge-id map are random byte reads, made anew by every slice: where they outgrow an on-chip copy, whole rows
+    // are the faster ones (67 M edges at mean degree 16, lane groups against blocks in ms: 1x128 2.64:2.55, 1x256 4.29:4.95, 1x512
+    // 7.58:9.79; 64 M edges, 3x128: 4.97:6.58; 115 M edges, 4x64: 4.82:5.48; 1.3 M edges, 1x256: 0.153:0.085).
+    if (a.eid && a.F > sw && a.nnz * heads > (int64_t(16) << 20)) sw = 0;
     if (sw) { /* every row length alike */ }
     else if (low_degree && small_graph && a.F <= 256) a.short_max = 64;
     else if (low_degree && !a.eid && a.F <= 512) a.short_max = tiny = (a.F <= 128 ? 8 : 4);
