@@ -528,7 +528,7 @@ def main():
         step = lambda: (T.tango_typed_layer_fwd(L), T.tango_typed_layer_bwd(L))
         heads = 1
         spmm = lambda: T.tango_qspmm(G, T.IN, 1, F, L["w_q"], L["s_w"], L["Hp_q"], L["s_Hp"], L["out"], L["absmax_out"])
-        spmm_name = "tango_qspmm, in-edge direction over (source, type) rows (k_spmm_short for rows of up to 64 edges, k_spmm for the rest, prepare/finalize)"
+        spmm_name = "tango_qspmm, in-edge direction over (source, type) rows (k_spmm_blocks, prepare/finalize)"
         alg = spmm_bytes(g.n_nodes, g.n_edges, heads, F)
         table_bytes = g.n_nodes * nt * F
     elif cfg["kind"] == "gcn":
@@ -542,7 +542,7 @@ def main():
         step = lambda: (T.tango_gcn_layer_fwd(L), T.tango_gcn_layer_bwd(L))
         heads, F = 1, cfg["dim"]
         spmm = lambda: T.tango_qspmm(G, T.IN, 1, F, L["w_q"], L["s_w"], L["Hp_q"], L["s_Hp"], L["out"], L["absmax_out"])
-        spmm_name = "tango_qspmm, in-edge direction (k_spmm_short for rows of up to 64 edges, k_spmm for the rest, prepare/finalize)"
+        spmm_name = "tango_qspmm, in-edge direction (k_spmm_blocks, prepare/finalize)"
         alg = spmm_bytes(g.n_nodes, g.n_edges, heads, F)
         table_bytes = g.n_nodes * F
     elif name == "gat_products":

@@ -209,7 +209,7 @@ int tango_qgemm_static(int64_t M, int64_t N, int64_t K, const float *A, const fl
  * gradients for the full-precision weight update).  dA or dB may be NULL to
  * skip that product.  dA with N > 2048 needs N % 16 == 0.
  * dB is a reduction over all M rows: slabs of at most 2^17 rows are summed in
- * int32 (exact: 2^17 * 127^2 < 2^31) and the slabs are combined in 64-bit
+ * int32 (exact: 2^17 * 127^2 < 2^31), stored in ws and summed in 64-bit
  * integers, so dB is the exact integer product for any M (for sums that fit
  * int32 -- every case the paper's 32-bit accumulator covers, Sec. 3.2 -- the
  * result is the same bit for bit).
@@ -397,7 +397,8 @@ int tango_gat_attention_fwd(const tango_graph *g, int heads, int dim, const int8
  *                             With alpha_q = NULL it may be NULL while dS and dD are given: then no edge tensor is
  *                             written at all - one walk over the in-edges forms P and dD from three running sums
  *                             per (node, head) (dD = B - P*C with P = sum alpha*dalpha, B = sum alpha*dalpha*s,
- *                             C = sum alpha*s, s = 1 or the slope by the sign of the score; fp64), and one walk
+ *                             C = sum alpha*s, s = 1 or the slope by the sign of the score; fp64 inside a wave,
+ *                             64-bit fixed point across waves, so independent of their order), and one walk
  *                             over the out-edges forms dX_agg and dS together;
  *   dD, dS (n x heads fp32) = sums over in-/out-edges of alpha*(dalpha - P)*lrelu'(t) with the fp32 alpha
  *                             recomputed from S_q, D_q, row_lse exactly as the forward pass computed it
